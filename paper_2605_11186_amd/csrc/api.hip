@@ -30,6 +30,7 @@ struct cats_ctx {
     float* x;        // [max_tree][H] residual stream
     // activations that feed a GEMM or the attention products: high and low bf16 parts
     bf16_t *xn, *xn_lo;      // [max_tree][H] rows times gain (norm factor applied downstream)
+    bf16_t* xp;              // the same rows in packed-X order (fused_row_blocks(max_tree) blocks of 16 rows)
     float* ss;               // [max_tree][SS_STRIDE] sums of squares per column block
     bf16_t *q, *q_lo;        // [max_tree][H] rotated queries
     bf16_t *attn, *attn_lo;  // [max_tree][H] attention output
@@ -233,6 +234,38 @@ GemmPlan enqueue_gemm(cats_ctx* c, const bf16_t* x, const bf16_t* x_lo, const vo
     return g.plan;
 }
 
+// The q|k|v and gate|up products with complete sums and the step behind them (FusedArgs); R: column
+// groups per workgroup.
+int fused_qkv_groups(const cats_ctx* c) { return ::fused_qkv_groups(3 * c->d.hidden / 16, c->n_cus, c->rows); }
+int fused_swiglu_groups(const cats_ctx* c) { return ::fused_swiglu_groups(c->d.ffn / 8, c->n_cus, c->rows); }
+FusedArgs fused_args(const cats_ctx* c, const void* w0, const void* w1, const void* w2, int groups) {
+    FusedArgs f{};
+    f.xp = c->xp;
+    f.w[0] = static_cast<const bf16_t*>(w0);
+    f.w[1] = static_cast<const bf16_t*>(w1);
+    f.w[2] = static_cast<const bf16_t*>(w2);
+    f.packed = c->d.packed_weights;
+    f.K = c->d.hidden;
+    f.T = c->rows;
+    f.groups = groups;
+    f.ns = norm_scale(c);
+    f.H = c->d.hidden;
+    f.d = c->d.head_dim;
+    f.hd_shift = c->d.head_dim == 128 ? 3 : 2;
+    f.max_ctx = c->d.max_ctx;
+    f.F = c->d.ffn;
+    return f;
+}
+template <class Launch>
+void enqueue_fused(cats_ctx* c, const FusedArgs& f, int R, Launch launch, hipStream_t st) {
+    if (c->prof_on && c->prof_n < CATS_PROF_MAX) {
+        launch(f, R, st, c->prof_ev[2 * c->prof_n], c->prof_ev[2 * c->prof_n + 1]);
+        ++c->prof_n;
+    } else {
+        launch(f, R, st, nullptr, nullptr);
+    }
+}
+
 // with_lo: the call's own rows (nodes n0 .. n0 + rows - 1) have their low parts in the window
 void enqueue_attention(cats_ctx* c, const bf16_t* q, const bf16_t* q_lo, const cats_kv_layer* kv,
                        int ctx_len, bf16_t* out, bf16_t* out_lo, bool with_lo, hipStream_t st) {
@@ -295,33 +328,54 @@ int enqueue_row_attention(cats_ctx* c, const float* part, const GemmPlan& plan, 
     return a.n_chunks;
 }
 
-// One decoder layer.  On entry c->xn holds rmsnorm(x)*g_attn of this layer; on
-// exit x is updated and, if next_gain is given, c->xn holds rmsnorm(x)*next_gain.
+// Where the norm in front of a layer's q|k|v product leaves its result: packed X or (null) c->xn
+bf16_t* layer_input_packed(const cats_ctx* c) { return fused_qkv_groups(c) ? c->xp : nullptr; }
+
+// One decoder layer.  On entry c->xn (or c->xp, see layer_input_packed) holds rmsnorm(x)*g_attn of
+// this layer; on exit x is updated and, if next_gain is given, c->xn (c->xp if next_layer: the
+// consumer is another layer and takes packed X) holds rmsnorm(x)*next_gain.
 void enqueue_layer(cats_ctx* c, const cats_layer_weights* w, float* x, const cats_kv_layer* kv,
-                   int ctx_len, const void* next_gain, hipStream_t st) {
+                   int ctx_len, const void* next_gain, bool next_layer, hipStream_t st) {
     const int H = c->d.hidden, F = c->d.ffn, T = c->rows;   // nodes n0 .. n0 + rows - 1
     // attention block
-    GemmPlan plan = enqueue_gemm(c, c->xn, c->xn_lo, w->wq, w->wk, w->wv, 3, H, H, st);
-    QkvRopeArgs qa;
-    qa.part = c->part;
-    qa.plan = plan;
-    qa.ns = norm_scale(c);
-    qa.cs = c->rope_cs + static_cast<size_t>(c->n0) * (c->d.head_dim / 2);
-    qa.q = c->q;
-    qa.q_lo = c->q_lo;
-    qa.kc = static_cast<bf16_t*>(kv->k);
-    qa.vt = static_cast<bf16_t*>(kv->v);
-    qa.T = T;
-    qa.H = H;
-    qa.nh = c->d.n_heads;
-    qa.d = c->d.head_dim;
-    qa.max_ctx = c->d.max_ctx;
-    qa.row0 = ctx_len + c->n0;
-    qa.k_lo = c->k_lo;
-    qa.vt_lo = c->vt_lo;
-    qa.win0 = ctx_len % ATTN_KB + c->n0;
+    GemmPlan plan{};
+    if (const int R = fused_qkv_groups(c)) {
+        FusedArgs f = fused_args(c, w->wq, w->wk, w->wv, 3 * H / 16);
+        f.cs = c->rope_cs + static_cast<size_t>(c->n0) * (c->d.head_dim / 2);
+        f.q = c->q;
+        f.q_lo = c->q_lo;
+        f.kc = static_cast<bf16_t*>(kv->k);
+        f.vt = static_cast<bf16_t*>(kv->v);
+        f.k_lo = c->k_lo;
+        f.vt_lo = c->vt_lo;
+        f.row0 = ctx_len + c->n0;
+        f.win0 = ctx_len % ATTN_KB + c->n0;
+        enqueue_fused(c, f, R, launch_fused_qkv, st);
+    } else {
+        plan = enqueue_gemm(c, c->xn, c->xn_lo, w->wq, w->wk, w->wv, 3, H, H, st);
+        if (T > 1) {
+            QkvRopeArgs qa;
+            qa.part = c->part;
+            qa.plan = plan;
+            qa.ns = norm_scale(c);
+            qa.cs = c->rope_cs + static_cast<size_t>(c->n0) * (c->d.head_dim / 2);
+            qa.q = c->q;
+            qa.q_lo = c->q_lo;
+            qa.kc = static_cast<bf16_t*>(kv->k);
+            qa.vt = static_cast<bf16_t*>(kv->v);
+            qa.T = T;
+            qa.H = H;
+            qa.nh = c->d.n_heads;
+            qa.d = c->d.head_dim;
+            qa.max_ctx = c->d.max_ctx;
+            qa.row0 = ctx_len + c->n0;
+            qa.k_lo = c->k_lo;
+            qa.vt_lo = c->vt_lo;
+            qa.win0 = ctx_len % ATTN_KB + c->n0;
+            launch_qkv_rope(qa, st);
+        }
+    }
     if (T > 1) {
-        launch_qkv_rope(qa, st);
         enqueue_attention(c, c->q, c->q_lo, kv, ctx_len, c->attn, c->attn_lo, true, st);
         plan = enqueue_gemm(c, c->attn, c->attn_lo, w->wo, nullptr, nullptr, 1, H, H, st);
     } else {
@@ -338,6 +392,9 @@ void enqueue_layer(cats_ctx* c, const cats_layer_weights* w, float* x, const cat
     rn.gain = static_cast<const bf16_t*>(has_ffn(w) ? w->g_ffn : next_gain);
     rn.xn = c->xn;
     rn.xn_lo = c->xn_lo;
+    bf16_t* next_xp = next_layer ? layer_input_packed(c) : nullptr;
+    const int R_ffn = fused_swiglu_groups(c);
+    rn.xp = has_ffn(w) ? (R_ffn ? c->xp : nullptr) : next_xp;
     rn.ss = c->ss;
     rn.T = T;
     rn.H = H;
@@ -345,20 +402,28 @@ void enqueue_layer(cats_ctx* c, const cats_layer_weights* w, float* x, const cat
     launch_residual_norm(rn, st);
     if (!has_ffn(w)) return;   // attention-only block
     // feed-forward block
-    plan = enqueue_gemm(c, c->xn, c->xn_lo, w->w_gate, w->w_up, nullptr, 2, F, H, st);
-    SwigluArgs sa;
-    sa.part = c->part;
-    sa.plan = plan;
-    sa.ns = norm_scale(c);
-    sa.h = c->hact;
-    sa.h_lo = c->hact_lo;
-    sa.T = T;
-    sa.F = F;
-    sa.f_pad = seg_pad_of(c, F);
-    launch_swiglu(sa, st);
+    if (R_ffn) {
+        FusedArgs f = fused_args(c, w->w_gate, w->w_up, nullptr, F / 8);
+        f.h = c->hact;
+        f.h_lo = c->hact_lo;
+        enqueue_fused(c, f, R_ffn, launch_fused_swiglu, st);
+    } else {
+        plan = enqueue_gemm(c, c->xn, c->xn_lo, w->w_gate, w->w_up, nullptr, 2, F, H, st);
+        SwigluArgs sa;
+        sa.part = c->part;
+        sa.plan = plan;
+        sa.ns = norm_scale(c);
+        sa.h = c->hact;
+        sa.h_lo = c->hact_lo;
+        sa.T = T;
+        sa.F = F;
+        sa.f_pad = seg_pad_of(c, F);
+        launch_swiglu(sa, st);
+    }
     plan = enqueue_gemm(c, c->hact, c->hact_lo, w->w_down, nullptr, nullptr, 1, H, F, st);
     rn.plan = plan;
     rn.gain = static_cast<const bf16_t*>(next_gain);
+    rn.xp = next_xp;
     launch_residual_norm(rn, st);
 }
 
@@ -577,6 +642,7 @@ int cats_create(const cats_model_desc* desc, cats_ctx** out) {
     const size_t o_anc = take(Tm * sizeof(u32x4));
     const size_t o_x = take(Tm * H * 4), o_xn = take(Tm * H * 2), o_q = take(Tm * H * 2);
     const size_t o_attn = take(Tm * H * 2), o_h = take(Tm * F * 2);
+    const size_t o_xp = take(static_cast<size_t>(fused_row_blocks(d.max_tree)) * 16 * H * 2 * 2);
     const size_t o_xn_lo = take(Tm * H * 2), o_q_lo = take(Tm * H * 2), o_attn_lo = take(Tm * H * 2);
     const size_t o_h_lo = take(Tm * F * 2);
     const size_t o_ss = take(Tm * SS_STRIDE * 4);
@@ -615,6 +681,7 @@ int cats_create(const cats_model_desc* desc, cats_ctx** out) {
     c->anc = reinterpret_cast<u32x4*>(b + o_anc);
     c->x = reinterpret_cast<float*>(b + o_x);
     c->xn = reinterpret_cast<bf16_t*>(b + o_xn);
+    c->xp = reinterpret_cast<bf16_t*>(b + o_xp);
     c->q = reinterpret_cast<bf16_t*>(b + o_q);
     c->attn = reinterpret_cast<bf16_t*>(b + o_attn);
     c->hact = reinterpret_cast<bf16_t*>(b + o_h);
@@ -707,6 +774,7 @@ int cats_verify_layer(cats_ctx* ctx, const cats_layer_weights* w, float* hidden,
     rn.gain = static_cast<const bf16_t*>(w->g_attn);
     rn.xn = ctx->xn;
     rn.xn_lo = ctx->xn_lo;
+    rn.xp = layer_input_packed(ctx);
     rn.ss = ctx->ss;
     rn.T = ctx->T;
     rn.H = ctx->d.hidden;
@@ -717,7 +785,7 @@ int cats_verify_layer(cats_ctx* ctx, const cats_layer_weights* w, float* hidden,
         enqueue_layer_row(ctx, w, kv, ctx_len, nullptr, st);
         finish_row(ctx, hidden, nullptr, st);
     } else {
-        enqueue_layer(ctx, w, hidden, kv, ctx_len, nullptr, st);
+        enqueue_layer(ctx, w, hidden, kv, ctx_len, nullptr, false, st);
     }
     HIP_TRY(hipGetLastError());
     return CATS_OK;
@@ -795,6 +863,7 @@ static void enqueue_rows_and_layers(cats_ctx* ctx, const cats_layer_weights* lay
     rn.gain = static_cast<const bf16_t*>(layer_end > layer_begin ? layers[layer_begin].g_attn : last_gain);
     rn.xn = ctx->xn;
     rn.xn_lo = ctx->xn_lo;
+    rn.xp = layer_end > layer_begin ? layer_input_packed(ctx) : nullptr;
     rn.ss = ctx->ss;
     rn.T = ctx->rows;
     rn.H = ctx->d.hidden;
@@ -814,7 +883,7 @@ static void enqueue_rows_and_layers(cats_ctx* ctx, const cats_layer_weights* lay
     }
     for (int l = layer_begin; l < layer_end; ++l) {
         const void* next_gain = (l + 1 < layer_end) ? layers[l + 1].g_attn : last_gain;
-        enqueue_layer(ctx, &layers[l], ctx->x, &kv[l], ctx_len, next_gain, st);
+        enqueue_layer(ctx, &layers[l], ctx->x, &kv[l], ctx_len, next_gain, l + 1 < layer_end, st);
     }
 }
 
@@ -1141,11 +1210,13 @@ int cats_verify_tree_streamed(cats_ctx* ctx, const cats_layer_weights* host_laye
         HIP_TRY(hipStreamWaitEvent(st, ctx->ev_copied[b], 0));
         const cats_layer_weights w = staged(b);
         rn.gain = static_cast<const bf16_t*>(w.g_attn);
+        rn.xp = layer_input_packed(ctx);
         launch_residual_norm(rn, st);
-        enqueue_layer(ctx, &w, ctx->x, &kv[l], ctx_len, nullptr, st);
+        enqueue_layer(ctx, &w, ctx->x, &kv[l], ctx_len, nullptr, false, st);
         HIP_TRY(hipEventRecord(ctx->ev_consumed[b], st));
     }
     rn.gain = static_cast<const bf16_t*>(g_final);
+    rn.xp = nullptr;
     launch_residual_norm(rn, st);
     if (hidden_out)
         HIP_TRY(hipMemcpyAsync(hidden_out, ctx->x, sizeof(float) * T * H, hipMemcpyDeviceToDevice, st));

@@ -258,6 +258,7 @@ struct ResidualNormArgs {
     const bf16_t* gain;     // optional [H]: if given, xn = x * gain (unscaled) and ss are written
     bf16_t* xn;             // [T][H] high parts of x * gain
     bf16_t* xn_lo;          // [T][H] low parts
+    bf16_t* xp = nullptr;   // if given, x * gain goes here in packed-X order instead of xn / xn_lo (see FusedArgs)
     float* ss;              // [T][SS_STRIDE] sums of squares of x per block of SS_COLS columns
     int T, H;
     float eps;
@@ -324,6 +325,39 @@ struct ArgmaxArgs {
 };
 constexpr int ARGMAX_SLICES = 16;
 void launch_argmax(const ArgmaxArgs& a, hipStream_t st);
+
+// ---------------------------------------------------------------- products with complete sums
+// The q|k|v and gate|up products with the step behind them (see fused.hpp).  X comes in fragment order
+// ("packed X"): element (t, k), part p (0 high, 1 low), at packed_x_offset(t, k, K) + 512 p.
+__host__ __device__ inline size_t packed_x_offset(int t, int k, int K) {
+    return (static_cast<size_t>(t >> 4) * (K >> 5) + (k >> 5)) * 1024 + ((t & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
+// 16-row blocks of X that a call with T rows reads: 1, 2, 3, 4, 6 or 8 (one kernel each)
+__host__ __device__ inline int fused_row_blocks(int T) {
+    const int m = (T + 15) / 16;
+    return m <= 4 ? m : (m <= 6 ? 6 : 8);
+}
+struct FusedArgs {
+    const bf16_t* xp;     // packed X, fused_row_blocks(T) blocks
+    const bf16_t* w[3];   // q, k, v or gate, up
+    int packed;           // weights are cats_pack_matrix outputs
+    int K, T;             // K a multiple of 64
+    int groups;           // column groups: 3 H / 16 or F / 8
+    NormScale ns;
+    // SwiGLU: h = silu(gate) * up
+    bf16_t *h, *h_lo;     // [T][F] high and low parts
+    int F;
+    // q|k|v: see QkvRopeArgs
+    const float2* cs;
+    bf16_t *q, *q_lo, *kc, *vt, *k_lo, *vt_lo;
+    int H, d, hd_shift, max_ctx, row0, win0;   // hd_shift: log2(d / 16)
+};
+// Column groups per workgroup (0: the product stays with the partial-tile kernel).  The smallest
+// count among the built ones with which one workgroup per compute unit covers the product.
+int fused_qkv_groups(int groups, int n_cus, int rows);
+int fused_swiglu_groups(int groups, int n_cus, int rows);
+void launch_fused_qkv(const FusedArgs& a, int R, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+void launch_fused_swiglu(const FusedArgs& a, int R, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
 // ---------------------------------------------------------------- single-row product
 // The same product for a single row (T = 1: the stage-1 draft loop and plain decoding), with the

@@ -12,7 +12,16 @@ namespace {
 // (row, block of 256 columns): nothing here needs a whole row, so the launch has T * H/256
 // independent waves.
 __global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualNormArgs a) {
-    const int t = blockIdx.x, blk = blockIdx.y;
+    int t = blockIdx.x, blk = blockIdx.y;
+    if (a.xp) {
+        // Packed X: a 128-byte line holds 16 bytes of each of eight rows.  The 16 rows of a block of
+        // columns run on one XCD (workgroup b runs on XCD b % 8), so that its L2 collects the whole line.
+        const int n_blk = (a.H + SS_COLS - 1) / SS_COLS;
+        const int pair = blockIdx.x / 128 * 8 + blockIdx.x % 8;   // (row group, block of columns)
+        blk = pair % n_blk;
+        t = pair / n_blk * 16 + blockIdx.x / 8 % 16;
+        if (t >= a.T) return;
+    }
     const int j = blk * SS_COLS + 4 * threadIdx.x;
     float ss = 0.f;
     if (j < a.H) {
@@ -33,8 +42,10 @@ __global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualNormArgs a) 
         if (a.gain) {
             uint2 hi, lo;
             gain_split4(val, *reinterpret_cast<const uint2*>(a.gain + j), hi, lo);
-            *reinterpret_cast<uint2*>(a.xn + row + j) = hi;
-            *reinterpret_cast<uint2*>(a.xn_lo + row + j) = lo;
+            bf16_t* out = a.xp ? a.xp + packed_x_offset(t, j, a.H) : a.xn + row + j;
+            bf16_t* out_lo = a.xp ? out + 512 : a.xn_lo + row + j;
+            *reinterpret_cast<uint2*>(out) = hi;
+            *reinterpret_cast<uint2*>(out_lo) = lo;
         }
     }
     if (!a.gain) return;
@@ -341,7 +352,10 @@ __global__ __launch_bounds__(AM_THREADS) void cats_argmax(ArgmaxArgs a) {
 }  // namespace
 
 void launch_residual_norm(const ResidualNormArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(cats_residual_rmsnorm, dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS), dim3(64), 0, st, a);
+    const int n_blk = (a.H + SS_COLS - 1) / SS_COLS;
+    const int pairs = (a.T + 15) / 16 * n_blk;   // packed X: see the kernel
+    const dim3 grid = a.xp ? dim3((pairs + 7) / 8 * 128) : dim3(a.T, n_blk);
+    hipLaunchKernelGGL(cats_residual_rmsnorm, grid, dim3(64), 0, st, a);
 }
 
 void launch_rope_table(const RopeTableArgs& a, hipStream_t st) {
