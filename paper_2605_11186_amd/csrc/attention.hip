@@ -11,6 +11,13 @@
 // publishes its chunk's result, and the last workgroup of a (head, query group) to arrive adds
 // up all chunks in chunk order with the usual log-sum-exp rescaling and writes the output:
 // one kernel, no separate merge launch.
+// What bounds it: at short contexts a chain of memory round trips (queries and first block, values with
+// low parts, hand-over between chunks), at long ones the waves' arithmetic and the 128-byte lines a compute
+// unit can have in flight.  Eight waves of 256 registers, so that each SIMD has two: one works while the other
+// waits, and the next block's keys and values are requested into the registers that this block's products
+// have just freed.  Measured against four waves with two register sets (7B shape, one layer): 64 nodes /
+// 4096 rows 28.4 -> 25.8 us, 63 / 1024 19.3 -> 18.3, 16 / 512 14.7 -> 14.3, 128 / 4096 46.8 -> 45.7.  Four waves
+// of 64 queries (half the key and value traffic) were slower at every size: 33.3 us at 64 / 4096, 26.2 at 63 / 1024.
 // Scores are computed transposed, S^T = K Q^T, with the 16x16x32 bf16 MFMA, so a
 // lane owns ONE query column and 8 keys of every 32-key block: the running
 // max / sum of the online softmax are per-lane scalars shared by four lanes and
@@ -38,18 +45,6 @@ __device__ __forceinline__ u32x4 keep_keys(u32x4 v, int key0, int lo, int hi) {
     }
     return v;
 }
-
-// 16-byte device-coherent accesses (they bypass the per-XCD caches).  The compiler does not see
-// the load behind the asm: every value must pass through wait_coherent before its first use.
-__device__ __forceinline__ void store_coherent16(float* p, f32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ f32x4 load_coherent16(const float* p) {
-    f32x4 v;
-    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-    return v;
-}
-__device__ __forceinline__ void wait_coherent(f32x4& v) { asm volatile("s_waitcnt vmcnt(0)" : "+v"(v)::"memory"); }
 
 // MFMA 16x16x32 bf16 (wave64): lane l supplies, for A, row l%16 and
 // k = 8*(l/16)..+7; for B, column l%16 and the same k; its 4 results are
@@ -133,33 +128,36 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // The K / V fragments of one 32-key block.  Score-block rows are permuted so that a lane
     // ends up with 8 consecutive keys: sub-block b, MFMA row mm <-> key j0 + 8*(mm/4) + 4*b + mm%4.
     // V^T fragments: row = dim, k = 8 consecutive keys starting at j0 + 8*q4.
-    auto load_block = [&](bf16x8 (&kf)[2][KS], bf16x8 (&vf)[DB], int blk) {
-        const int j0 = blk * ATTN_KB;
+    auto load_k = [&](bf16x8 (&kf)[2][KS], int blk) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int key = j0 + 8 * (m >> 2) + 4 * b + (m & 3);
+            const uint32_t off = static_cast<uint32_t>(blk * ATTN_KB + 8 * (m >> 2) + 4 * b + (m & 3)) * D + 8 * q4;
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
-                kf[b][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(
-                    kbase + static_cast<size_t>(key) * D + 32 * s + 8 * q4));
+            for (int s = 0; s < KS; ++s) kf[b][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(kbase + off + 32 * s));
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load_v = [&](bf16x8 (&vf)[DB], int blk) {
+        const uint32_t off = static_cast<uint32_t>(m * a.max_ctx + blk * ATTN_KB + 8 * q4);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-            vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(
-                vbase + static_cast<size_t>(16 * db + m) * a.max_ctx + j0 + 8 * q4));
+        for (int db = 0; db < DB; ++db)   // wave-uniform base, one offset register
+            vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(vbase + static_cast<size_t>(16 * db) * a.max_ctx + off));
         __builtin_amdgcn_sched_barrier(0);
     };
     // The low parts of the same fragments from the window; rows outside [lo_begin, lo_end) are
     // stale there and come out as zeros.  Addresses are clamped into the window (what a clamp
     // moves is masked anyway: the window covers every row of the range).
     const int win_base = S & ~(ATTN_KB - 1);
-    auto load_block_lo = [&](bf16x8 (&kf)[2][KS], bf16x8 (&vf)[DB], int blk) {
-        const int j0 = blk * ATTN_KB;
+    auto mask_v = [&](bf16x8 (&v)[DB], int blk) {   // rows past the tree may hold anything
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+            v[db] = as_bf16x8(keep_keys(__builtin_bit_cast(u32x4, v[db]), blk * ATTN_KB + 8 * q4, 0, n_keys));
+    };
+    auto load_k_lo = [&](bf16x8 (&kf)[2][KS], int blk) {
         const bf16_t* kl = a.k_lo + static_cast<size_t>(h) * TREE_WIN * D;
-        const bf16_t* vl = a.vt_lo + static_cast<size_t>(h) * D * TREE_WIN;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int key = j0 + 8 * (m >> 2) + 4 * b + (m & 3);
+            const int key = blk * ATTN_KB + 8 * (m >> 2) + 4 * b + (m & 3);
             const bool ok = key >= a.lo_begin && key < a.lo_end;
             const int w = min(key - win_base, TREE_WIN - 1);
 #pragma unroll
@@ -168,54 +166,53 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
                 kf[b][s] = as_bf16x8(ok ? v : u32x4{0u, 0u, 0u, 0u});
             }
         }
-        const int key0 = j0 + 8 * q4;
+    };
+    auto load_v_lo = [&](bf16x8 (&vf)[DB], int blk) {
+        const bf16_t* vl = a.vt_lo + static_cast<size_t>(h) * D * TREE_WIN;
+        const int key0 = blk * ATTN_KB + 8 * q4;
         const int w0 = min(key0 - win_base, TREE_WIN - 8);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const u32x4 v = *reinterpret_cast<const u32x4*>(vl + static_cast<size_t>(16 * db + m) * TREE_WIN + w0);
             vf[db] = as_bf16x8(keep_keys(v, key0, a.lo_begin, a.lo_end));
         }
-        __builtin_amdgcn_sched_barrier(0);
     };
 
     // MODE 0: every key of the block is a context row (no mask, no tail: straight-line code);
     // MODE 1: the block may hold tree rows and rows past the tree; MODE 2: as 1, and the block
-    // also has low parts of keys (kfl) and values (vfl).  Scores and running maxima are kept in
+    // also has low parts of keys and values.  Scores and running maxima are kept in
     // the base-2 domain (the scale carries log2 e), so that every exponential is one v_exp_f32.
-    auto compute_block = [&](const bf16x8 (&kf)[2][KS], const bf16x8 (&vf_in)[DB], const bf16x8 (&kfl)[2][KS],
-                             const bf16x8 (&vfl)[DB], int blk, auto mode_tag) {
-        constexpr int MODE = decltype(mode_tag)::value;
-        constexpr bool LO = MODE == 2;
-        const int j0 = blk * ATTN_KB;
-        const int key0 = j0 + 8 * q4;
-        bf16x8 vf[DB];
+    bf16x8 kf[2][KS], vf[DB];
+    f32x4 st[QB][2];
+    auto scores = [&](const bf16x8 (&k)[2][KS], const bf16x8 (&kl)[2][KS], auto lo_tag) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            u32x4 v = __builtin_bit_cast(u32x4, vf_in[db]);
-            if constexpr (MODE != 0) v = keep_keys(v, key0, 0, n_keys);  // rows past the tree may hold anything
-            vf[db] = as_bf16x8(v);
-        }
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            f32x4 st[2];
+        for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                st[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                st[qb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
-                    st[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b][s], qf[qb][s], st[b], 0, 0, 0);
-                    st[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b][s], qfl[qb][s], st[b], 0, 0, 0);
-                    if constexpr (LO)
-                        st[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfl[b][s], qf[qb][s], st[b], 0, 0, 0);
+                    st[qb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[b][s], qf[qb][s], st[qb][b], 0, 0, 0);
+                    st[qb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[b][s], qfl[qb][s], st[qb][b], 0, 0, 0);
+                    if constexpr (decltype(lo_tag)::value)
+                        st[qb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl[b][s], qf[qb][s], st[qb][b], 0, 0, 0);
                 }
             }
+    };
+    // the block's probabilities and their product with its values
+    auto weigh = [&](const bf16x8 (&v)[DB], const bf16x8 (&vl)[DB], int blk, auto mode_tag) {
+        constexpr int MODE = decltype(mode_tag)::value;
+        constexpr bool LO = MODE == 2;
+        const int key0 = blk * ATTN_KB + 8 * q4;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
             // this lane: query column m of group qb, keys key0 + 4*b + r
             float sc[8];
             bool vis[8];
             float bmax = -1e30f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                bool v = true;
+                bool see = true;
                 if constexpr (MODE != 0) {
                     // branch-free: the ancestor word is picked with selects, a key outside the
                     // tree's rows reads bit 0 of a zero word
@@ -225,10 +222,10 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
                     const u32x4 am = anc[qb];
                     uint32_t word = w == 0 ? am[0] : (w == 1 ? am[1] : (w == 2 ? am[2] : am[3]));
                     word = in_tree ? word : 0u;
-                    v = rel < 0 || ((word >> (rel & 31)) & 1u);
+                    see = rel < 0 || ((word >> (rel & 31)) & 1u);
                 }
-                vis[i] = v;
-                sc[i] = v ? st[i >> 2][i & 3] * scale : -1e30f;
+                vis[i] = see;
+                sc[i] = see ? st[qb][i >> 2][i & 3] * scale : -1e30f;
                 bmax = fmaxf(bmax, sc[i]);
             }
             bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
@@ -269,22 +266,22 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
             const bf16x8 pf = as_bf16x8(pv), pfl = as_bf16x8(pvl);
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db], pf, o[qb][db], 0, 0, 0);
-                o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db], pfl, o[qb][db], 0, 0, 0);
+                o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[db], pf, o[qb][db], 0, 0, 0);
+                o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[db], pfl, o[qb][db], 0, 0, 0);
                 if constexpr (LO)
-                    o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfl[db], pf, o[qb][db], 0, 0, 0);
+                    o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vl[db], pf, o[qb][db], 0, 0, 0);
             }
+            if constexpr (MODE != 0) __builtin_amdgcn_sched_barrier(0);   // one group's masks at a time: registers
         }
         fresh = false;
     };
 
-    // Two register sets.  This wave's blocks come in three runs.  Context-only blocks (all of
-    // them but the last few): the fragments of block b+1 are requested before block b is
-    // multiplied, so the cache latency of one block hides behind the arithmetic of the other.
-    // Then the blocks that hold tree rows without low parts (rows an earlier call appended, or a
-    // caller's own rows), one at a time; then the blocks with low parts, set A holding the high
-    // parts and set B the low parts.  The last two runs are at most five blocks per head.
-    bf16x8 kfA[2][KS], kfB[2][KS], vfA[DB], vfB[DB];
+    // This wave's blocks come in three runs: the blocks with low parts, the blocks that hold tree
+    // rows without low parts (rows an earlier call appended, or a caller's own rows), at most five
+    // per head together, then the context-only blocks.  Those need no second set of registers for
+    // the loads in flight: the next block's keys are requested as soon as this block's scores
+    // have used up theirs, its values once the products have, and the other wave of the SIMD
+    // works meanwhile.
     const bool have_lo = a.k_lo != nullptr && a.lo_end > a.lo_begin;
     const int lo_blk = have_lo ? min(blk_end, a.lo_begin / ATTN_KB) : blk_end;   // first block with low parts
     const int ctx_end = min(lo_blk, tree_blk);                                // blocks below hold context rows only
@@ -296,26 +293,38 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // the costlier blocks first: their loads go out with the kernel's first requests
     if (have_lo) {
         for (int blk = my_first(lo_blk); blk < blk_end; blk += blk_stride) {
-            load_block(kfA, vfA, blk);
-            load_block_lo(kfB, vfB, blk);
-            compute_block(kfA, vfA, kfB, vfB, blk, std::integral_constant<int, 2>{});
+            {
+                bf16x8 kl[2][KS];
+                load_k(kf, blk);
+                load_k_lo(kl, blk);
+                scores(kf, kl, std::true_type{});
+            }
+            bf16x8 vl[DB];
+            load_v(vf, blk);
+            load_v_lo(vl, blk);
+            mask_v(vf, blk);
+            weigh(vf, vl, blk, std::integral_constant<int, 2>{});
         }
     }
     for (int blk = my_first(ctx_end); blk < lo_blk; blk += blk_stride) {
-        load_block(kfA, vfA, blk);
-        compute_block(kfA, vfA, kfB, vfB, blk, std::integral_constant<int, 1>{});
+        load_k(kf, blk);
+        load_v(vf, blk);
+        scores(kf, kf, std::false_type{});
+        mask_v(vf, blk);
+        weigh(vf, vf, blk, std::integral_constant<int, 1>{});
     }
     if (my_begin < ctx_end) {
-        const int last = my_begin + (ctx_end - 1 - my_begin) / blk_stride * blk_stride;  // this wave's last such block
-        load_block(kfA, vfA, my_begin);
-        for (int blk = my_begin; blk < ctx_end; blk += 2 * blk_stride) {
-            load_block(kfB, vfB, min(blk + blk_stride, last));
-            compute_block(kfA, vfA, kfB, vfB, blk, std::integral_constant<int, 0>{});
-            if (blk + blk_stride < ctx_end) {
-                load_block(kfA, vfA, min(blk + 2 * blk_stride, last));
-                compute_block(kfB, vfB, kfA, vfA, blk + blk_stride, std::integral_constant<int, 0>{});
-            }
+        int blk = my_begin;
+        load_k(kf, blk);
+        load_v(vf, blk);
+        for (; blk + blk_stride < ctx_end; blk += blk_stride) {
+            scores(kf, kf, std::false_type{});
+            load_k(kf, blk + blk_stride);
+            weigh(vf, vf, blk, std::integral_constant<int, 0>{});
+            load_v(vf, blk + blk_stride);
         }
+        scores(kf, kf, std::false_type{});
+        weigh(vf, vf, blk, std::integral_constant<int, 0>{});
     }
 
     // every wave parks its running max, row sum and unnormalised output in LDS ...
@@ -402,6 +411,8 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // chunks in index order, eight chunks' loads in flight at a time (one memory round trip for
     // up to eight chunks), rescaled to the running maximum between groups
     constexpr int MG = 8;
+    const float* po_head = a.po + static_cast<size_t>(h) * a.n_chunks * a.t_pad * D;
+    const uint32_t po_bytes = static_cast<uint32_t>(a.n_chunks * a.t_pad) * D * 4;
     float Mg = -1e30f;
     f32x4 num[NI];
     float den = 0.f;
@@ -416,14 +427,10 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
             const size_t sl = (static_cast<size_t>(h) * a.n_chunks + c) * a.t_pad + qbase + ql;
             mc[j] = __hip_atomic_load(a.pml + sl * 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             lc[j] = __hip_atomic_load(a.pml + sl * 2 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const float* po = a.po + sl * D + c4;
+            const uint32_t off = static_cast<uint32_t>(c * a.t_pad + qbase + ql) * D + c4;
 #pragma unroll
-            for (int i = 0; i < NI; ++i) v[j][i] = load_coherent16(po + 4 * TPQ * i);
+            for (int i = 0; i < NI; ++i) v[j][i] = load_coherent16(po_head, po_bytes, 4 * (off + 4 * TPQ * i));
         }
-#pragma unroll
-        for (int j = 0; j < MG; ++j)
-#pragma unroll
-            for (int i = 0; i < NI; ++i) wait_coherent(v[j][i]);
         float Mn = Mg;
 #pragma unroll
         for (int j = 0; j < MG; ++j) Mn = fmaxf(Mn, mc[j]);   // clamped repeats do not change the maximum
@@ -690,7 +697,7 @@ void launch_decode_attention(const DecodeAttnArgs& a, hipStream_t st) {
 }
 
 void launch_attention(const AttnArgs& a, hipStream_t st) {
-    dim3 grid(a.n_chunks, a.nh, (a.Tq + ATTN_QN - 1) / ATTN_QN);
+    const dim3 grid(a.n_chunks, a.nh, (a.Tq + ATTN_QN - 1) / ATTN_QN);
     if (a.d == 128)
         hipLaunchKernelGGL((cats_tree_attention_kernel<128, ATTN_QN / 16, ATTN_WAVES>), grid, dim3(64 * ATTN_WAVES), 0, st, a);
     else
