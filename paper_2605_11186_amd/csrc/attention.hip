@@ -128,20 +128,26 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // The K / V fragments of one 32-key block.  Score-block rows are permuted so that a lane
     // ends up with 8 consecutive keys: sub-block b, MFMA row mm <-> key j0 + 8*(mm/4) + 4*b + mm%4.
     // V^T fragments: row = dim, k = 8 consecutive keys starting at j0 + 8*q4.
+    // Element numbers inside a head take 64 bits (2^25 keys of 128 are 2^32).  Keys shift the key number; values add the
+    // block to the head's base as a scalar, and only m max_ctx + 8 q4 stays in vector registers.  That is as fast as 32-bit
+    // numbers (7B shape, 63 nodes / 1024 rows: 13.7 us a launch in a row of launches); the values' whole number in vector
+    // registers spills 24 of them, and a scalar wave index from the kernel's head on costs 0.3 us.
     auto load_k = [&](bf16x8 (&kf)[2][KS], int blk) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const uint32_t off = static_cast<uint32_t>(blk * ATTN_KB + 8 * (m >> 2) + 4 * b + (m & 3)) * D + 8 * q4;
+            const uint32_t key = blk * ATTN_KB + 8 * (m >> 2) + 4 * b + (m & 3);
+            const size_t off = static_cast<size_t>(key) * D + 8 * q4;
 #pragma unroll
             for (int s = 0; s < KS; ++s) kf[b][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(kbase + off + 32 * s));
         }
         __builtin_amdgcn_sched_barrier(0);
     };
+    const size_t v_lane = static_cast<size_t>(m) * a.max_ctx + 8 * q4;
     auto load_v = [&](bf16x8 (&vf)[DB], int blk) {
-        const uint32_t off = static_cast<uint32_t>(m * a.max_ctx + blk * ATTN_KB + 8 * q4);
+        const bf16_t* vb = vbase + __builtin_amdgcn_readfirstlane(blk * ATTN_KB);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)   // wave-uniform base, one offset register
-            vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(vbase + static_cast<size_t>(16 * db) * a.max_ctx + off));
+        for (int db = 0; db < DB; ++db)
+            vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(16 * db) * a.max_ctx + v_lane));
         __builtin_amdgcn_sched_barrier(0);
     };
     // The low parts of the same fragments from the window; rows outside [lo_begin, lo_end) are

@@ -43,3 +43,48 @@ def test_long_chunks(heads, d, T, S):
     # one bf16 rounding of the output (2^-9 of each entry), everything before it at 16 bits or more
     assert torch.isfinite(got).all()
     assert float((got - ref).norm() / ref.norm()) <= 2.0 ** -9
+
+
+def _one_head(d, max_ctx, k_rows):
+    """One head's zeroed keys and values of which only the first k_rows rows are ever visible."""
+    k = torch.empty(1, max_ctx, d, dtype=torch.bfloat16, device="cuda")
+    v = torch.empty(1, d, max_ctx, dtype=torch.bfloat16, device="cuda")
+    k[:, :k_rows] = 0
+    v[..., :k_rows] = 0
+    return k, v
+
+
+def _attend_to_one_row_each(d, max_ctx, S, rows):
+    """Query t matches the key of row rows[t] alone (its score is about 8 sqrt(d), all others stay below half
+    of it), so that the output is that row's value."""
+    T = len(rows)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    k, v = _one_head(d, max_ctx, S + T)
+    q = torch.empty(T, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    want = torch.empty(T, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    for t, r in enumerate(rows):
+        k[0, r] = 8 * q[t]
+        v[0, :, r] = want[t]
+    ctx = cats.cats_create(cats.ModelDesc(1, d, 1, d, 64, 64, max_ctx, T, 1e-6, 10000.0, 0))
+    try:
+        out = torch.zeros_like(q)
+        parent = np.arange(T, dtype=np.int32) - 1
+        cats.cats_set_tree(ctx, np.zeros(T, np.int32), parent, np.arange(T, dtype=np.int32), torch.cuda.current_stream())
+        cats.cats_tree_attention(ctx, q, cats.KVLayer(k.data_ptr(), v.data_ptr()), S, out, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+    finally:
+        cats.cats_destroy(ctx)
+    assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_keys_past_32_bit_element_offsets(d):
+    """Rows on both sides of the one whose first element is number 2^32 of its head, and the last one."""
+    first = 2 ** 32 // d
+    S = first + 100
+    _attend_to_one_row_each(d, (S + 4 + 63) // 64 * 64, S, [first - 1, first, first + 1, S - 1])
+
+
+def test_value_rows_past_32_bit_element_offsets():
+    """A cache so wide that dimension 15 of a 16-dimension block starts past element 2^32 of the block."""
+    _attend_to_one_row_each(64, (2 ** 32 // 15 + 64) // 64 * 64, 70, [0, 33, 69])
