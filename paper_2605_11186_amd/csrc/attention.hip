@@ -46,6 +46,19 @@ __device__ __forceinline__ u32x4 keep_keys(u32x4 v, int key0, int lo, int hi) {
     return v;
 }
 
+// 16-byte device-coherent store: it goes past the XCD's L2
+__device__ __forceinline__ void store_coherent16(float* p, f32x4 v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+}
+
+// 16-byte device-coherent load (sc1: it bypasses the per-XCD caches) at a byte offset from a base that is
+// the same for the whole wave; a builtin, so that the compiler knows when the value has arrived.
+constexpr int AUX_SC1 = 16;
+__device__ __forceinline__ f32x4 load_coherent16(const float* base, uint32_t bytes, uint32_t offset) {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, bytes, 0x00027000);
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, AUX_SC1));
+}
+
 // MFMA 16x16x32 bf16 (wave64): lane l supplies, for A, row l%16 and
 // k = 8*(l/16)..+7; for B, column l%16 and the same k; its 4 results are
 // D[4*(l/16) + r][l%16].

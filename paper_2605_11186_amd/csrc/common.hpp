@@ -31,19 +31,6 @@ __device__ __forceinline__ void split_bf2(float a, float b, uint32_t& hi, uint32
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// 16-byte device-coherent store: it goes past the XCD's L2
-__device__ __forceinline__ void store_coherent16(float* p, f32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
-}
-
-// 16-byte device-coherent load (sc1: it bypasses the per-XCD caches) at a byte offset from a base that is
-// the same for the whole wave; a builtin, so that the compiler knows when the value has arrived.
-constexpr int AUX_SC1 = 16;
-__device__ __forceinline__ f32x4 load_coherent16(const float* base, uint32_t bytes, uint32_t offset) {
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, bytes, 0x00027000);
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, AUX_SC1));
-}
-
 // ---------------------------------------------------------------- GEMM
 // Y[t][n] = sum_k X[t][k] * W[n][k] for t < T.  The work is the list of
 // (row tile, K chunk) items in tile-major order, cut into n_wgs equal contiguous

@@ -56,7 +56,6 @@ __global__ __launch_bounds__(64 * W) void cats_gemm_rows(FusedArgs a) {
     const int S = a.K / 32, C = (a.K + GEMM_KC - 1) / GEMM_KC;
     const int s0 = S * wave / W, n = S * (wave + 1) / W - s0;   // this wave's k steps (none if K is tiny)
     const int last = max(n - 1, 0);
-    (void)C;
 
     const bf16_t* wp[R];
 #pragma unroll

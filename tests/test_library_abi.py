@@ -25,6 +25,11 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(lib, name), name
 
 
+def test_every_kernel_source_is_built():
+    from paper_2605_11186_amd import build
+    assert sorted(build.SOURCES) == sorted(p.name for p in (build.PKG / "csrc").glob("*.hip"))
+
+
 def test_status_strings_and_kernel_name():
     assert cats.cats_strerror(cats.CATS_OK) == "ok"
     assert "max_ctx" in cats.cats_strerror(cats.CATS_ECAPACITY)
