@@ -15,7 +15,8 @@
 // low parts, hand-over between chunks), at long ones the waves' arithmetic and the 128-byte lines a compute
 // unit can have in flight.  Eight waves of 256 registers, so that each SIMD has two: one works while the other
 // waits, and the next block's keys and values are requested into the registers that this block's products
-// have just freed.  Measured against four waves with two register sets (7B shape, one layer): 64 nodes /
+// have just freed.  (head_dim 128: 8 registers spill around the run of blocks with low parts, at most one or two blocks of a
+// wave, and none in the context loop; head_dim 64: none.)  Measured against four waves with two register sets (7B shape, one layer): 64 nodes /
 // 4096 rows 28.4 -> 25.8 us, 63 / 1024 19.3 -> 18.3, 16 / 512 14.7 -> 14.3, 128 / 4096 46.8 -> 45.7.  Four waves
 // of 64 queries (half the key and value traffic) were slower at every size: 33.3 us at 64 / 4096, 26.2 at 63 / 1024.
 // Scores are computed transposed, S^T = K Q^T, with the 16x16x32 bf16 MFMA, so a
@@ -142,9 +143,9 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // ends up with 8 consecutive keys: sub-block b, MFMA row mm <-> key j0 + 8*(mm/4) + 4*b + mm%4.
     // V^T fragments: row = dim, k = 8 consecutive keys starting at j0 + 8*q4.
     // Element numbers inside a head take 64 bits (2^25 keys of 128 are 2^32).  Keys shift the key number; values add the
-    // block to the head's base as a scalar, and only m max_ctx + 8 q4 stays in vector registers.  That is as fast as 32-bit
-    // numbers (7B shape, 63 nodes / 1024 rows: 13.7 us a launch in a row of launches); the values' whole number in vector
-    // registers spills 24 of them, and a scalar wave index from the kernel's head on costs 0.3 us.
+    // block to the head's base as a scalar.  A lane's place in the values is formed anew at every load (the empty
+    // asm keeps it there): kept in two registers for the whole kernel it costs 0.5-1 us a launch inside a layer (7B shape,
+    // 16 nodes / 512 rows, small weights: 70.7 us a layer with it kept, 69.2 with 32-bit numbers, 68.4 so).
     auto load_k = [&](bf16x8 (&kf)[2][KS], int blk) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -155,9 +156,11 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    const size_t v_lane = static_cast<size_t>(m) * a.max_ctx + 8 * q4;
     auto load_v = [&](bf16x8 (&vf)[DB], int blk) {
         const bf16_t* vb = vbase + __builtin_amdgcn_readfirstlane(blk * ATTN_KB);
+        int m_here = m;
+        asm volatile("" : "+v"(m_here));
+        const size_t v_lane = static_cast<size_t>(m_here) * a.max_ctx + 8 * q4;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
             vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(16 * db) * a.max_ctx + v_lane));
@@ -172,6 +175,7 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         for (int db = 0; db < DB; ++db)
             v[db] = as_bf16x8(keep_keys(__builtin_bit_cast(u32x4, v[db]), blk * ATTN_KB + 8 * q4, 0, n_keys));
     };
+    // (32-bit offsets: the window of a head is small, and fewer address registers spill)
     auto load_k_lo = [&](bf16x8 (&kf)[2][KS], int blk) {
         const bf16_t* kl = a.k_lo + static_cast<size_t>(h) * TREE_WIN * D;
 #pragma unroll
@@ -181,7 +185,7 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
             const int w = min(key - win_base, TREE_WIN - 1);
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const u32x4 v = *reinterpret_cast<const u32x4*>(kl + static_cast<size_t>(w) * D + 32 * s + 8 * q4);
+                const u32x4 v = *reinterpret_cast<const u32x4*>(kl + static_cast<uint32_t>(w * D + 32 * s + 8 * q4));
                 kf[b][s] = as_bf16x8(ok ? v : u32x4{0u, 0u, 0u, 0u});
             }
         }
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         const int w0 = min(key0 - win_base, TREE_WIN - 8);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(vl + static_cast<size_t>(16 * db + m) * TREE_WIN + w0);
+            const u32x4 v = *reinterpret_cast<const u32x4*>(vl + static_cast<uint32_t>((16 * db + m) * TREE_WIN + w0));
             vf[db] = as_bf16x8(keep_keys(v, key0, a.lo_begin, a.lo_end));
         }
     };
