@@ -15,7 +15,7 @@
 // low parts, hand-over between chunks), at long ones the waves' arithmetic and the 128-byte lines a compute
 // unit can have in flight.  Eight waves of 256 registers, so that each SIMD has two: one works while the other
 // waits, and the next block's keys and values are requested into the registers that this block's products
-// have just freed.  (head_dim 128: 8 registers spill around the run of blocks with low parts, at most one or two blocks of a
+// have just freed.  (head_dim 128: 10 registers spill around the run of blocks with low parts, at most one or two blocks of a
 // wave, and none in the context loop; head_dim 64: none.)  Measured against four waves with two register sets (7B shape, one layer): 64 nodes /
 // 4096 rows 28.4 -> 25.8 us, 63 / 1024 19.3 -> 18.3, 16 / 512 14.7 -> 14.3, 128 / 4096 46.8 -> 45.7.  Four waves
 // of 64 queries (half the key and value traffic) were slower at every size: 33.3 us at 64 / 4096, 26.2 at 63 / 1024.
@@ -142,28 +142,34 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // The K / V fragments of one 32-key block.  Score-block rows are permuted so that a lane
     // ends up with 8 consecutive keys: sub-block b, MFMA row mm <-> key j0 + 8*(mm/4) + 4*b + mm%4.
     // V^T fragments: row = dim, k = 8 consecutive keys starting at j0 + 8*q4.
-    // Element numbers inside a head take 64 bits (2^25 keys of 128 are 2^32).  Keys shift the key number; values add the
-    // block to the head's base as a scalar.  A lane's place in the values is formed anew at every load (the empty
-    // asm keeps it there): kept in two registers for the whole kernel it costs 0.5-1 us a launch inside a layer (7B shape,
-    // 16 nodes / 512 rows, small weights: 70.7 us a layer with it kept, 69.2 with 32-bit numbers, 68.4 so).
+    // Element numbers inside a head take 64 bits (2^25 keys of 128 are 2^32): a block's place is added to the head's
+    // base as a scalar, a lane's place inside a key block takes 32.  A lane's row of values is formed anew at every
+    // load where registers are short (head_dim 128; the empty asm keeps it there) and kept as a pointer where they
+    // are not.  Launches inside a layer against 32-bit numbers (which are wrong there), us: 32 heads of 128, 16 nodes, 512
+    // rows 13.9 -> 13.6, 1024 rows 14.6 -> 14.3, 4096 rows 21.8 -> 21.2; with the values' row kept 14.5, 15.6, 22.7.
+    // Heads of 64: the same within 1 % either way over 36 sizes.
     auto load_k = [&](bf16x8 (&kf)[2][KS], int blk) {
+        const bf16_t* kb = kbase + static_cast<size_t>(__builtin_amdgcn_readfirstlane(blk)) * (ATTN_KB * D);
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const uint32_t key = blk * ATTN_KB + 8 * (m >> 2) + 4 * b + (m & 3);
-            const size_t off = static_cast<size_t>(key) * D + 8 * q4;
+            const uint32_t off = static_cast<uint32_t>(8 * (m >> 2) + 4 * b + (m & 3)) * D + 8 * q4;
 #pragma unroll
-            for (int s = 0; s < KS; ++s) kf[b][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(kbase + off + 32 * s));
+            for (int s = 0; s < KS; ++s) kf[b][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(kb + off + 32 * s));
         }
         __builtin_amdgcn_sched_barrier(0);
     };
+    const bf16_t* v_row = vbase + static_cast<size_t>(m) * a.max_ctx + 8 * q4;
     auto load_v = [&](bf16x8 (&vf)[DB], int blk) {
-        const bf16_t* vb = vbase + __builtin_amdgcn_readfirstlane(blk * ATTN_KB);
-        int m_here = m;
-        asm volatile("" : "+v"(m_here));
-        const size_t v_lane = static_cast<size_t>(m_here) * a.max_ctx + 8 * q4;
+        const bf16_t* vb = v_row + static_cast<uint32_t>(blk * ATTN_KB);
+        if constexpr (D == 128) {
+            int m_here = m;
+            asm volatile("" : "+v"(m_here));
+            const size_t v_lane = static_cast<size_t>(m_here) * a.max_ctx + 8 * q4;
+            vb = vbase + __builtin_amdgcn_readfirstlane(blk * ATTN_KB) + v_lane;
+        }
 #pragma unroll
         for (int db = 0; db < DB; ++db)
-            vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(16 * db) * a.max_ctx + v_lane));
+            vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(16 * db) * a.max_ctx));
         __builtin_amdgcn_sched_barrier(0);
     };
     // The low parts of the same fragments from the window; rows outside [lo_begin, lo_end) are
@@ -175,7 +181,6 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         for (int db = 0; db < DB; ++db)
             v[db] = as_bf16x8(keep_keys(__builtin_bit_cast(u32x4, v[db]), blk * ATTN_KB + 8 * q4, 0, n_keys));
     };
-    // (32-bit offsets: the window of a head is small, and fewer address registers spill)
     auto load_k_lo = [&](bf16x8 (&kf)[2][KS], int blk) {
         const bf16_t* kl = a.k_lo + static_cast<size_t>(h) * TREE_WIN * D;
 #pragma unroll
@@ -185,18 +190,21 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
             const int w = min(key - win_base, TREE_WIN - 1);
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const u32x4 v = *reinterpret_cast<const u32x4*>(kl + static_cast<uint32_t>(w * D + 32 * s + 8 * q4));
+                const u32x4 v = *reinterpret_cast<const u32x4*>(kl + static_cast<size_t>(w) * D + 32 * s + 8 * q4);
                 kf[b][s] = as_bf16x8(ok ? v : u32x4{0u, 0u, 0u, 0u});
             }
         }
     };
     auto load_v_lo = [&](bf16x8 (&vf)[DB], int blk) {
+        // (the window of a head is small: 32-bit offsets where registers are short)
         const bf16_t* vl = a.vt_lo + static_cast<size_t>(h) * D * TREE_WIN;
         const int key0 = blk * ATTN_KB + 8 * q4;
         const int w0 = min(key0 - win_base, TREE_WIN - 8);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(vl + static_cast<uint32_t>((16 * db + m) * TREE_WIN + w0));
+            const u32x4 v = *reinterpret_cast<const u32x4*>(
+                D == 128 ? vl + static_cast<uint32_t>((16 * db + m) * TREE_WIN + w0)
+                         : vl + static_cast<size_t>(16 * db + m) * TREE_WIN + w0);
             vf[db] = as_bf16x8(keep_keys(v, key0, a.lo_begin, a.lo_end));
         }
     };
