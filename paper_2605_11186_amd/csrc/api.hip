@@ -236,8 +236,12 @@ GemmPlan enqueue_gemm(cats_ctx* c, const bf16_t* x, const bf16_t* x_lo, const vo
 
 // The q|k|v and gate|up products with complete sums and the step behind them (FusedArgs); R: column
 // groups per workgroup.
-int fused_qkv_groups(const cats_ctx* c) { return ::fused_qkv_groups(3 * c->d.hidden / 16, c->n_cus, c->rows); }
-int fused_swiglu_groups(const cats_ctx* c) { return ::fused_swiglu_groups(c->d.ffn / 8, c->n_cus, c->rows); }
+int fused_qkv_groups(const cats_ctx* c) {
+    return ::fused_qkv_groups({3 * c->d.hidden / 16, c->d.hidden, c->rows, c->n_cus, c->d.packed_weights != 0});
+}
+int fused_swiglu_groups(const cats_ctx* c) {
+    return ::fused_swiglu_groups({c->d.ffn / 8, c->d.hidden, c->rows, c->n_cus, c->d.packed_weights != 0});
+}
 FusedArgs fused_args(const cats_ctx* c, const void* w0, const void* w1, const void* w2, int groups) {
     FusedArgs f{};
     f.xp = c->xp;

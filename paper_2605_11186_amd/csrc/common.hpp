@@ -352,10 +352,14 @@ struct FusedArgs {
     bf16_t *q, *q_lo, *kc, *vt, *k_lo, *vt_lo;
     int H, d, hd_shift, max_ctx, row0, win0;   // hd_shift: log2(d / 16)
 };
-// Column groups per workgroup (0: the product stays with the partial-tile kernel).  The smallest
-// count among the built ones with which one workgroup per compute unit covers the product.
-int fused_qkv_groups(int groups, int n_cus, int rows);
-int fused_swiglu_groups(int groups, int n_cus, int rows);
+// Column groups per workgroup: the smallest count among the built ones with which one workgroup per compute
+// unit covers the product; 0: the product stays with the partial-tile kernel (the rules say where).
+struct FusedRule {
+    int groups, K, rows, n_cus;
+    bool packed;
+};
+int fused_qkv_groups(const FusedRule& p);
+int fused_swiglu_groups(const FusedRule& p);
 void launch_fused_qkv(const FusedArgs& a, int R, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 void launch_fused_swiglu(const FusedArgs& a, int R, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 

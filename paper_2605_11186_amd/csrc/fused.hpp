@@ -13,7 +13,7 @@
 // contiguous kilobyte per wave load.  At the end the waves' sums meet in LDS.  A column group is eight rows
 // of one place in the weights and eight of another (gate and up rows of the same columns; the two
 // halves of a rotation pair), so that whatever the step behind the product combines is inside one group
-// and any number of groups makes a workgroup: R is picked so that the launch fills the chip once.
+// and any number of groups makes a workgroup: R is the smallest count with which the chip holds all of them at once.
 //
 // Measured on the 7B shape, kernel times: gate|up (180 MB of weights) 31 us at 16 rows, 40 at 63, 60 at 128;
 // q|k|v (100 MB) 20 / 30 / 46 us.  The growth with the rows is not matrix time (17 % of the cycles at 63 rows): a
