@@ -99,8 +99,7 @@ inline size_t align256(size_t n) { return (n + 255) & ~static_cast<size_t>(255);
 int target_wgs(const cats_ctx* c) { return c->n_cus; }
 
 // Key chunks per (head, query group): the launch has heads * query groups * chunks workgroups,
-// about one per compute unit (the kernel's register footprint allows one four-wave workgroup
-// per unit); more chunks than that only add hand-over traffic between workgroups.
+// about one per compute unit; more chunks than that only add hand-over traffic between workgroups.
 int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_keys) {
     const int n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
     const int groups = (rows + ATTN_QN - 1) / ATTN_QN;

@@ -5,20 +5,19 @@
 // on its root-to-node path.  The ancestor sets are 128-bit masks, built from parent[] in
 // LDS by cats_tree_masks when the tree is uploaded and read here one mask per query.
 //
-// Work split: one workgroup of ATTN_WAVES waves per (head, chunk of key blocks, group of
-// ATTN_QN queries); wave w takes the chunk's blocks w, w + ATTN_WAVES, ... and the waves'
+// Work split: one workgroup of W waves per (head, chunk of key blocks, group of
+// ATTN_QN queries); wave w takes the chunk's blocks w, w + W, ... and the waves'
 // partial results are merged through LDS.  With more than one chunk the workgroup then
 // publishes its chunk's result, and the last workgroup of a (head, query group) to arrive adds
 // up all chunks in chunk order with the usual log-sum-exp rescaling and writes the output:
 // one kernel, no separate merge launch.
 // What bounds it: at short contexts a chain of memory round trips (queries and first block, values with
 // low parts, hand-over between chunks), at long ones the waves' arithmetic and the 128-byte lines a compute
-// unit can have in flight.  Eight waves of 256 registers, so that each SIMD has two: one works while the other
-// waits, and the next block's keys and values are requested into the registers that this block's products
-// have just freed.  (head_dim 128: 10 registers spill around the run of blocks with low parts, at most one or two blocks of a
-// wave, and none in the context loop; head_dim 64: none.)  Measured against four waves with two register sets (7B shape, one layer): 64 nodes /
-// 4096 rows 28.4 -> 25.8 us, 63 / 1024 19.3 -> 18.3, 16 / 512 14.7 -> 14.3, 128 / 4096 46.8 -> 45.7.  Four waves
-// of 64 queries (half the key and value traffic) were slower at every size: 33.3 us at 64 / 4096, 26.2 at 63 / 1024.
+// unit can have in flight.  One register set: the next block's keys and values are requested into the registers that
+// this block's products have just freed.  Four or eight waves, see launch_attention.  With eight waves and head_dim 128
+// the 256 registers of a wave do not quite do: 10 spill around the run of blocks with low parts (at most one or two blocks of a
+// wave), none in the context loop.  Four waves of 64 queries (half the key and value traffic) were slower than
+// eight waves of 32 at every size: 33.3 against 25.8 us at 64 nodes / 4096 rows, 26.2 against 18.3 at 63 / 1024.
 // Scores are computed transposed, S^T = K Q^T, with the 16x16x32 bf16 MFMA, so a
 // lane owns ONE query column and 8 keys of every 32-key block: the running
 // max / sum of the online softmax are per-lane scalars shared by four lanes and
@@ -727,10 +726,17 @@ void launch_decode_attention(const DecodeAttnArgs& a, hipStream_t st) {
         hipLaunchKernelGGL((cats_decode_attention<64>), grid, dim3(256), 0, st, a);
 }
 
+// Waves per workgroup.  Head size 128: four, without a spill; eight where a head has more than eight chunks, which its
+// last workgroup then merges in more than one round (twice the threads halve that).  Launches inside a layer, four with
+// two register sets (as it was) -> eight -> four, us: 32 heads, 16 nodes / 512 rows 14.5 -> 13.6 -> 12.5, 33 / 97 13.4 -> 13.8 -> 11.7, 63 /
+// 1024 18.4 -> 17.3 -> 15.2, 63 / 4096 29.6 -> 29.8 -> 25.9, 128 / 4096 47.6 -> 46.6 -> 44.1; 8 heads, 16 nodes (32 chunks at 1024 rows and
+// more) / 512 rows 15.7 -> 13.9 -> 14.4, / 4096 21.5 -> 17.6 -> 19.0.  Head size 64 (no spill, half the LDS): eight, by 2.5 to 4 %.
 void launch_attention(const AttnArgs& a, hipStream_t st) {
     const dim3 grid(a.n_chunks, a.nh, (a.Tq + ATTN_QN - 1) / ATTN_QN);
-    if (a.d == 128)
-        hipLaunchKernelGGL((cats_tree_attention_kernel<128, ATTN_QN / 16, ATTN_WAVES>), grid, dim3(64 * ATTN_WAVES), 0, st, a);
+    if (a.d == 64)
+        hipLaunchKernelGGL((cats_tree_attention_kernel<64, ATTN_QN / 16, 8>), grid, dim3(512), 0, st, a);
+    else if (a.n_chunks > 8)
+        hipLaunchKernelGGL((cats_tree_attention_kernel<128, ATTN_QN / 16, 8>), grid, dim3(512), 0, st, a);
     else
-        hipLaunchKernelGGL((cats_tree_attention_kernel<64, ATTN_QN / 16, ATTN_WAVES>), grid, dim3(64 * ATTN_WAVES), 0, st, a);
+        hipLaunchKernelGGL((cats_tree_attention_kernel<128, ATTN_QN / 16, 4>), grid, dim3(256), 0, st, a);
 }

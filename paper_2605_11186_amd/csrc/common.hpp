@@ -445,9 +445,8 @@ struct AttnArgs {
     bf16_t* out_lo;         // optional [Tq][H] low parts of the output
 };
 constexpr int ATTN_KB = 32;    // keys per block
-// An attention workgroup: ATTN_WAVES waves, each taking every ATTN_WAVES-th key block of the
-// workgroup's chunk for all ATTN_QN queries of the workgroup (two 16-query groups per wave).
-constexpr int ATTN_WAVES = 8;
+// An attention workgroup: four or eight waves (see launch_attention), each taking every fourth or eighth key
+// block of the workgroup's chunk for all ATTN_QN queries of the workgroup (two 16-query groups per wave).
 constexpr int ATTN_QN = 32;
 constexpr int ATTN_MAX_QGROUPS = CATS_MAX_TREE / ATTN_QN;   // query groups per head at most
 // Attention of a single-row call (one query node, T = 1 per step: the stage-1 draft loop, plain

@@ -88,3 +88,10 @@ def test_keys_past_32_bit_element_offsets(d):
 def test_value_rows_past_32_bit_element_offsets():
     """A cache so wide that dimension 15 of a 16-dimension block starts past element 2^32 of the block."""
     _attend_to_one_row_each(64, (2 ** 32 // 15 + 64) // 64 * 64, 70, [0, 33, 69])
+
+
+@pytest.mark.parametrize("heads,d,T,S", [(28, 128, 32, 1500), (32, 128, 32, 1500), (8, 128, 64, 700), (8, 128, 65, 700),
+                                         (28, 128, 3, 255), (28, 128, 2, 286), (1, 128, 128, 4000)])
+def test_both_wave_counts(heads, d, T, S):
+    """Either side of the line between four and eight waves: by heads, by query groups and by key blocks."""
+    test_long_chunks(heads, d, T, S)
