@@ -9,8 +9,8 @@ dispatch begin).  `traffic` reads the counter_collection.csv files of two runs o
 one with `--pmc FETCH_SIZE` and one with `--pmc WRITE_SIZE` (`--output-format csv`), scales both
 counters by what they read for a plain copy kernel of known size in the same run
 (`bench.py --calibrate-copy`: one 1 GiB device-to-device copy) and prints the HBM bytes per
-dispatch for every kernel, per launch of the weight-streaming GEMM, and per verify step (all
-`cats_*` kernels of one step; steps are counted by the one `cats_accept` dispatch each has).
+dispatch for every kernel, per launch of the weight-streaming products (mean over the dispatches of
+all `cats_gemm*` kernels), and per verify step (all `cats_*` kernels of one step; steps are counted by the one `cats_accept` dispatch each has).
 Nothing here touches a GPU: it only reads files.
 """
 from __future__ import annotations
@@ -69,7 +69,7 @@ def traffic(fetch_csv: str, write_csv: str) -> str:
            "",
            f"{'kernel (mean per dispatch)':64s} {'dispatches':>10s} {'per step':>9s} {'read MB':>9s} {'written MB':>11s}"]
     step_bytes = 0.0
-    gemm = None
+    gemm_n, gemm_rd, gemm_wr = 0, 0.0, 0.0   # all product kernels together
     for k in sorted(fetch, key=lambda k: -mean(fetch[k]) * len(fetch[k])):
         if "cats_" not in k:
             continue
@@ -81,11 +81,13 @@ def traffic(fetch_csv: str, write_csv: str) -> str:
         if "pack_matrix" not in k:
             step_bytes += (rd + wr) * per_step
         if "cats_gemm" in k:
-            gemm = (rd, wr)
+            gemm_n += n
+            gemm_rd += n * rd
+            gemm_wr += n * wr
     out.append("")
-    if gemm:
-        out.append(f"GEMM: {gemm[0] / 1e6:.1f} MB read + {gemm[1] / 1e6:.1f} MB written per launch")
-        out.append(f"gemm_traffic_bytes_per_launch: {int(gemm[0] + gemm[1])}")
+    if gemm_n:
+        out.append(f"products (cats_gemm*): {gemm_rd / gemm_n / 1e6:.1f} MB read + {gemm_wr / gemm_n / 1e6:.1f} MB written per launch")
+        out.append(f"gemm_traffic_bytes_per_launch: {int((gemm_rd + gemm_wr) / gemm_n)}")
     if steps:
         out.append(f"{steps} verify steps in the run; all cats_* kernels of one step (without the one-time weight re-tiling):")
         out.append(f"step_traffic_bytes: {int(step_bytes)}")

@@ -28,6 +28,19 @@ def test_traffic_is_scaled_by_the_copy_kernel_and_summed_per_step(tmp_path):
     assert "fetch x2.0000, write x1.0000" in text
 
 
+def test_traffic_per_launch_is_the_mean_over_all_product_kernels(tmp_path):
+    part = "void (anonymous namespace)::cats_gemm_skinny_bf16<2, 8, 1, 2, true, 1>(GemmArgs)"
+    rows = "void (anonymous namespace)::cats_gemm_rows<6, 4, 8, 1, true, 1>(FusedArgs)"
+    acc = "(anonymous namespace)::cats_accept(int const*)"
+    copy = ("__amd_rocclr_copyBuffer", 1048576.0)   # both scales are one
+    _csv(tmp_path / "f.csv", [copy, (acc, 0.0), (rows, 9000.0)] + [(part, 1000.0)] * 3)
+    _csv(tmp_path / "w.csv", [copy, (acc, 0.0), (rows, 40.0)] + [(part, 400.0)] * 3)
+    text = rs.traffic(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"))
+    total = (9040.0 + 3 * 1400.0) * 1024
+    assert f"gemm_traffic_bytes_per_launch: {int(total / 4)}" in text
+    assert f"step_traffic_bytes: {int(total)}" in text
+
+
 def test_kernel_trace_table(tmp_path):
     db = tmp_path / "t.db"
     con = sqlite3.connect(db)
