@@ -471,8 +471,8 @@ def main():
     ms_per_step = float(np.median(per_step))
     accepted = cats.accept_result_from_tensor(res_dev)
 
-    # Same K steps again with HIP events around every GEMM launch (on the launch stream): the
-    # dominant kernel's average duration.  Kept out of the region above so that the event
+    # Same K steps again with HIP events around every product launch (on the launch stream): the
+    # products' average duration.  Kept out of the region above so that the event
     # records do not inflate `value`.
     cats.cats_profile_gemm(ctx, True)
     gemm_ms, gemm_launches = 0.0, 0
@@ -528,7 +528,9 @@ def main():
                      "traffic": step_traffic,
                      "traffic_over_algorithmic": None if step_traffic is None else round(step_traffic / (w_bytes + kv_bytes), 3),
                      "traffic_source": None if step_traffic is None else f"profiles/{prof.name} (committed rocprofv3 --pmc summary, all kernels of one step)"},
-        "roofline": {"bound": "hbm", "kernel": cats.cats_gemm_kernel_name(),
+        "roofline": {"bound": "hbm", "kernel": f"cats_gemm_rows + {cats.cats_gemm_kernel_name()}",
+                     "note": "mean over all products of a step; cats_gemm_rows (q|k|v and gate|up where it is the faster one) includes "
+                             "the step behind the product: rotation and cache append, or SwiGLU",
                      "achieved": round(gemm_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gemm_gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_source": None if traffic is None else f"profiles/{prof.name} (committed rocprofv3 --pmc summary)",
@@ -558,7 +560,7 @@ def main():
                           "copy_link_gbs": round((w_bytes - dims.vocab * dims.hidden * 2) / t_copy / 1e9, 2),
                           "gemm_compute_s_per_step": round(gemm_ms * 1e-3 / args.steps, 5),
                           "exposed_beyond_copy_s": round(max(0.0, t_step - t_copy), 5)}
-        out["roofline"]["note"] = "offload regime: the step is bound by the host link, not by HBM"
+        out["roofline"]["note"] += "; offload regime: the step is bound by the host link, not by HBM"
     if not args.no_cpu_baseline:
         from oracle.cats_oracle import Oracle
         orc = Oracle(dims, host_layers + [None] * (L - n_keep), final, embed, precision="f32")

@@ -320,8 +320,9 @@ int cats_tree_attention_noalloc(const void *q, const cats_kv_layer *kv, const in
                                 int32_t n_nodes, int32_t n_heads, int32_t head_dim, int32_t max_ctx,
                                 int32_t ctx_len, void *out, void *stream);
 
-/* Measurement aid for the weight-streaming GEMM (the layer-weight pass of the
- * "Target verification pass"): while enabled, every GEMM launch made through
+/* Measurement aid for the weight-streaming products (the layer-weight pass of the
+ * "Target verification pass"; a product that rotates and appends to the cache, or applies SwiGLU,
+ * is timed with that step): while enabled, every product launch made through
  * this context carries a pair of HIP events attached to its dispatch on its own
  * stream (kernel begin / end; at most 1024 launches between two reads).  cats_profile_gemm_read waits for them and
  * returns the summed kernel time in milliseconds and the launch count (HOST
@@ -329,8 +330,8 @@ int cats_tree_attention_noalloc(const void *q, const cats_kv_layer *kv, const in
 int cats_profile_gemm(cats_ctx *ctx, int enable);
 int cats_profile_gemm_read(cats_ctx *ctx, float *total_ms, int32_t *launches);
 
-/* Name of the dominant (weight-streaming) kernel as it appears in profiler
- * output, and the text of a status code.  HOST strings, never freed. */
+/* Name of the weight-streaming kernel that ends with partial tiles (the one that ends with complete
+ * sums is cats_gemm_rows) as it appears in profiler output, and the text of a status code.  HOST strings, never freed. */
 const char *cats_gemm_kernel_name(void);
 const char *cats_strerror(int status);
 
