@@ -3,8 +3,8 @@
 // product (rotation and cache append for q|k|v, SwiGLU for gate|up) is carried out on them before
 // anything is written: no partial tiles, no row kernel.
 //
-// What bounds it: HBM for the weights up to about 32 rows, beyond that also the L2 -> CU traffic of X
-// (every workgroup reads all of it: 16 M rows x K x 4 bytes) and the matrix pipe.
+// What bounds it: HBM for the weights up to about 32 rows, beyond that the cache lines that a compute unit can have on
+// their way: every workgroup requests all of X (16 M rows x K x 4 bytes) beside its weights.
 //
 // Split.  A workgroup owns R column groups of 16 for the whole of K; its W waves split K, each one
 // streaming its own weight and activation fragments from memory straight into MFMA operand registers
@@ -16,9 +16,9 @@
 // and any number of groups makes a workgroup: R is the smallest count with which the chip holds all of them at once.
 //
 // Measured on the 7B shape, kernel times: gate|up (180 MB of weights) 31 us at 16 rows, 40 at 63, 60 at 128;
-// q|k|v (100 MB) 20 / 30 / 46 us.  The growth with the rows is not matrix time (17 % of the cycles at 63 rows): a
-// compute unit has about 75 cache lines on their way at any time, and every line of X takes one for some 300
-// cycles beside the weights' lines with 1000.
+// q|k|v (100 MB) 20 / 30 / 46 us.  The growth with the rows is not matrix time (16 and 22 % of the cycles at 64 rows, 30 at
+// 128): time = (lines of W x 1000 cycles + lines of X x 240) / (compute units x 58 to 96 lines on their way), by the
+// counters of L1 requests and their latency, within 5 % at 64 and 128 rows.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -234,7 +234,8 @@ __global__ __launch_bounds__(64 * W) void cats_gemm_rows(FusedArgs a) {
 // Waves and ring depth: eight waves (two per SIMD, 256 registers each: one multiplies while the other
 // waits) with the deepest ring that fits, else four waves with up to 512 registers.  Depths are powers of
 // two so that they divide a wave's step count at the usual widths (K = 4096: 16 steps on eight
-// waves); a depth of 3 or 5 there costs 4-10 % in reloads at the range's end.
+// waves); a depth of 3 or 5 there costs 4-10 % in reloads at the range's end.  (Beyond 96 rows gate|up with R = 8, and with
+// R = 7 on row-major weights, still spills two to five registers.)
 template <int R, int M>
 struct Shape {
     static constexpr int regs(int depth) { return 4 * R * M + 4 * depth * (R + 2 * M) + 2 * R + 28; }
