@@ -10,6 +10,8 @@
 // the partial-tile product holds three accumulator blocks a wave and is at its worst.  The line follows 110
 // widths from 256 to 8192 at 13 row counts: on its wrong side are at most 2.5 % of a layer.  Row-major weights: the
 // partial-tile product is so much slower that fused won at all but 2 % of the points, and lost 1.9 % at most there.
+// More than four groups (hidden beyond 5461 on 256 units) are not built yet. Measured there, packed (us): hidden 8192 with six
+// -7.7 of 154 at 16 rows, -4.4 at 64, -5.8 at 128; hidden 6144 with five -2.2 at 16, +0.4 at 64, +7.3 at 128.
 int fused_qkv_groups(const FusedRule& p) {
     if (p.rows < 2) return 0;   // a single row has kernels of its own
     for (int R : {1, 2, 3, 4}) {
