@@ -335,10 +335,10 @@ int enqueue_row_attention(cats_ctx* c, const float* part, const GemmPlan& plan, 
 bf16_t* layer_input_packed(const cats_ctx* c) { return fused_qkv_groups(c) ? c->xp : nullptr; }
 
 // One decoder layer.  On entry c->xn (or c->xp, see layer_input_packed) holds rmsnorm(x)*g_attn of
-// this layer; on exit x is updated and, if next_gain is given, c->xn (c->xp if next_layer: the
-// consumer is another layer and takes packed X) holds rmsnorm(x)*next_gain.
-void enqueue_layer(cats_ctx* c, const cats_layer_weights* w, float* x, const cats_kv_layer* kv,
-                   int ctx_len, const void* next_gain, bool next_layer, hipStream_t st) {
+// this layer; on exit x (x_out, if given) holds the updated rows and, if next_gain is given, c->xn (c->xp if
+// next_layer: the consumer is another layer and takes packed X) holds rmsnorm(x)*next_gain.
+void enqueue_layer(cats_ctx* c, const cats_layer_weights* w, float* x, const cats_kv_layer* kv, int ctx_len,
+                   const void* next_gain, bool next_layer, hipStream_t st, float* x_out = nullptr) {
     const int H = c->d.hidden, F = c->d.ffn, T = c->rows;   // nodes n0 .. n0 + rows - 1
     // attention block
     GemmPlan plan{};
@@ -402,6 +402,7 @@ void enqueue_layer(cats_ctx* c, const cats_layer_weights* w, float* x, const cat
     rn.T = T;
     rn.H = H;
     rn.eps = c->d.rms_eps;
+    rn.x_out = has_ffn(w) ? nullptr : x_out;
     launch_residual_norm(rn, st);
     if (!has_ffn(w)) return;   // attention-only block
     // feed-forward block
@@ -427,6 +428,7 @@ void enqueue_layer(cats_ctx* c, const cats_layer_weights* w, float* x, const cat
     rn.plan = plan;
     rn.gain = static_cast<const bf16_t*>(next_gain);
     rn.xp = next_xp;
+    rn.x_out = x_out;
     launch_residual_norm(rn, st);
 }
 
@@ -480,7 +482,7 @@ void finish_row(cats_ctx* c, float* dst, const void* gain, hipStream_t st) {
     c->row.pend = nullptr;
 }
 
-void enqueue_rope_table(cats_ctx* c, int ctx_len, hipStream_t st) {
+RopeTableArgs rope_table_args(const cats_ctx* c, int ctx_len) {
     RopeTableArgs r;
     r.depth = c->depth;
     r.cs = c->rope_cs;
@@ -488,18 +490,22 @@ void enqueue_rope_table(cats_ctx* c, int ctx_len, hipStream_t st) {
     r.d = c->d.head_dim;
     r.ctx_len = ctx_len;
     r.base = c->d.rope_base;
-    launch_rope_table(r, st);
+    return r;
 }
+
+// Rows that a kernel can write with 16-byte stores; any other place gets them by a copy.
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // typical: also the per-node log-sum-exp / entropy and, per node, whether its token passes the
 // typical criterion at its parent (needs the whole tree as rows)
-void enqueue_lm_head(cats_ctx* c, const void* w_lm, float* logits_out, int32_t* argmax_out,
-                     float* margin_out, hipStream_t st, bool typical = false) {
+// row_out (a single row with its residual update pending): where the product leaves the updated row
+void enqueue_lm_head(cats_ctx* c, const void* w_lm, float* logits_out, int32_t* argmax_out, float* margin_out,
+                     hipStream_t st, bool typical = false, float* row_out = nullptr) {
     GemmPlan plan;
     const float* part = c->part;
     if (c->rows == 1) {
         // with a residual update pending, it and the final norm ride in the product
-        GemvArgs g = c->row.pend ? gemv_norm(c, c->row.next_gain, nullptr) : gemv_plain(c->xn, c->xn_lo);
+        GemvArgs g = c->row.pend ? gemv_norm(c, c->row.next_gain, row_out) : gemv_plain(c->xn, c->xn_lo);
         // Only the greedy token wanted, and every workgroup of the product ends up with complete
         // sums (true of the 7B and 13B shapes on 256 compute units): the product picks it itself.
         if (!logits_out && !margin_out && !typical &&
@@ -556,9 +562,8 @@ void enqueue_lm_head(cats_ctx* c, const void* w_lm, float* logits_out, int32_t* 
     }
 }
 
-void enqueue_compact(cats_ctx* c, const cats_kv_layer* kv, int layer_begin, int layer_end, int ctx_len,
-                     const cats_accept_result* res_dev, hipStream_t st) {
-    if (layer_end <= layer_begin) return;
+CompactArgs compact_args(const cats_ctx* c, const cats_kv_layer* kv, int layer_begin, int layer_end, int ctx_len,
+                         const cats_accept_result* res_dev) {
     CompactArgs ca;
     ca.n_layers = layer_end - layer_begin;
     for (int l = layer_begin; l < layer_end; ++l) {
@@ -570,15 +575,26 @@ void enqueue_compact(cats_ctx* c, const cats_kv_layer* kv, int layer_begin, int 
     ca.max_ctx = c->d.max_ctx;
     ca.ctx_len = ctx_len;
     ca.res = res_dev;
-    launch_compact(ca, st);
+    return ca;
 }
 
 int enqueue_accept_compact(cats_ctx* c, const int32_t* amax, const cats_kv_layer* kv, int layer_begin,
                            int layer_end, int ctx_len, cats_accept_result* out_dev,
                            cats_accept_result* out_host, hipStream_t st, bool typical = false) {
-    launch_accept(c->token, c->parent, c->depth, amax, typical ? c->typ_edge : nullptr, c->T, ctx_len, out_dev,
-                  st);
-    enqueue_compact(c, kv, layer_begin, layer_end, ctx_len, out_dev, st);
+    AcceptArgs aa;
+    aa.token = c->token;
+    aa.parent = c->parent;
+    aa.depth = c->depth;
+    aa.amax = amax;
+    aa.edge_ok = typical ? c->typ_edge : nullptr;
+    aa.T = c->T;
+    aa.ctx_len = ctx_len;
+    aa.out = out_dev;
+    // a lone root is committed where it is: nothing to roll back
+    if (layer_end > layer_begin && c->T > 1)
+        launch_accept_compact(aa, compact_args(c, kv, layer_begin, layer_end, ctx_len, out_dev), st);
+    else
+        launch_accept(aa, st);
     HIP_TRY(hipGetLastError());
     if (out_host) {
         HIP_TRY(hipMemcpyAsync(out_host, out_dev, sizeof(cats_accept_result), hipMemcpyDeviceToHost, st));
@@ -751,8 +767,7 @@ int cats_set_tree(cats_ctx* ctx, const cats_tree* tree, void* stream) {
     std::memcpy(up.token, tree->token, sizeof(int32_t) * n);
     std::memcpy(up.parent, tree->parent, sizeof(int32_t) * n);
     std::memcpy(up.depth, tree->depth, sizeof(int32_t) * n);
-    launch_tree_upload(up, n, ctx->token, ctx->parent, ctx->depth, as_stream(stream));
-    launch_tree_masks(ctx->parent, n, ctx->anc, as_stream(stream));
+    launch_tree_upload(up, n, ctx->token, ctx->parent, ctx->depth, ctx->anc, as_stream(stream));
     HIP_TRY(hipGetLastError());
     std::memcpy(ctx->h_parent, tree->parent, sizeof(int32_t) * n);
     std::memcpy(ctx->h_depth, tree->depth, sizeof(int32_t) * n);
@@ -766,7 +781,6 @@ int cats_verify_layer(cats_ctx* ctx, const cats_layer_weights* w, float* hidden,
     if (rc != CATS_OK) return rc;
     if (!layer_ok(w) || !hidden || !kv_ok(kv, 0, 1)) return CATS_EINVAL;
     hipStream_t st = as_stream(stream);
-    enqueue_rope_table(ctx, ctx_len, st);
     ResidualNormArgs rn;
     rn.x = hidden;
     rn.x_in = nullptr;
@@ -782,7 +796,7 @@ int cats_verify_layer(cats_ctx* ctx, const cats_layer_weights* w, float* hidden,
     rn.T = ctx->T;
     rn.H = ctx->d.hidden;
     rn.eps = ctx->d.rms_eps;
-    launch_residual_norm(rn, st);
+    launch_rows_begin(rn, rope_table_args(ctx, ctx_len), st);
     if (ctx->rows == 1) {
         ctx->row.x = hidden;
         enqueue_layer_row(ctx, w, kv, ctx_len, nullptr, st);
@@ -850,28 +864,37 @@ int cats_lm_head_argmax(cats_ctx* ctx, const float* hidden, int32_t n_rows, cons
 }
 
 // Rows n0..T-1 of the residual stream from the embedding table or from the caller's rows, plus
-// the first layer's normalised input; then layers [layer_begin, layer_end).
-static void enqueue_rows_and_layers(cats_ctx* ctx, const cats_layer_weights* layers, int layer_begin,
+// the first layer's normalised input; then layers [layer_begin, layer_end).  The rows after the last layer
+// are to go to hidden_out, if given.  True: the last launch writes them there (a single row with last_gain:
+// the LM head's product will, see enqueue_lm_head); false: they end in ctx->x (ctx->row.x), to be copied.
+static bool enqueue_rows_and_layers(cats_ctx* ctx, const cats_layer_weights* layers, int layer_begin,
                                     int layer_end, const void* embed, const float* hidden_in,
                                     const void* last_gain, const cats_kv_layer* kv, int ctx_len,
-                                    hipStream_t st) {
-    enqueue_rope_table(ctx, ctx_len, st);
-    ResidualNormArgs rn;
-    rn.x = ctx->x;
-    rn.x_in = hidden_in;
-    rn.embed = static_cast<const bf16_t*>(embed);
-    rn.token = ctx->token + ctx->n0;
-    rn.part = nullptr;
-    rn.plan = GemmPlan{1, GEMM_KC, 1, 1, 1};
-    rn.gain = static_cast<const bf16_t*>(layer_end > layer_begin ? layers[layer_begin].g_attn : last_gain);
-    rn.xn = ctx->xn;
-    rn.xn_lo = ctx->xn_lo;
-    rn.xp = layer_end > layer_begin ? layer_input_packed(ctx) : nullptr;
-    rn.ss = ctx->ss;
-    rn.T = ctx->rows;
-    rn.H = ctx->d.hidden;
-    rn.eps = ctx->d.rms_eps;
-    launch_residual_norm(rn, st);
+                                    float* hidden_out, hipStream_t st) {
+    const bool any = layer_end > layer_begin;
+    float* x_out = any && aligned16(hidden_out) ? hidden_out : nullptr;
+    if (ctx->rows == 1 && embed && any) {   // the first product reads the embedding row itself
+        launch_rope_table(rope_table_args(ctx, ctx_len), st);
+        ctx->row.embed = static_cast<const bf16_t*>(embed);
+        ctx->row.token = ctx->token + ctx->n0;
+    } else {
+        ResidualNormArgs rn;
+        rn.x = ctx->x;
+        rn.x_in = hidden_in;
+        rn.embed = static_cast<const bf16_t*>(embed);
+        rn.token = ctx->token + ctx->n0;
+        rn.part = nullptr;
+        rn.plan = GemmPlan{1, GEMM_KC, 1, 1, 1};
+        rn.gain = static_cast<const bf16_t*>(any ? layers[layer_begin].g_attn : last_gain);
+        rn.xn = ctx->xn;
+        rn.xn_lo = ctx->xn_lo;
+        rn.xp = any ? layer_input_packed(ctx) : nullptr;
+        rn.ss = ctx->ss;
+        rn.T = ctx->rows;
+        rn.H = ctx->d.hidden;
+        rn.eps = ctx->d.rms_eps;
+        launch_rows_begin(rn, rope_table_args(ctx, ctx_len), st);
+    }
     if (ctx->rows == 1) {
         // single row: the last layer's residual update stays pending for the LM head's product
         // (which also leaves the final row in ctx->row.x), or is carried out here if none follows
@@ -881,13 +904,15 @@ static void enqueue_rows_and_layers(cats_ctx* ctx, const cats_layer_weights* lay
         if (last_gain)
             ctx->row.next_gain = last_gain;
         else
-            finish_row(ctx, ctx->x, nullptr, st);
-        return;
+            finish_row(ctx, x_out ? x_out : ctx->x, nullptr, st);
+        return x_out != nullptr;
     }
     for (int l = layer_begin; l < layer_end; ++l) {
-        const void* next_gain = (l + 1 < layer_end) ? layers[l + 1].g_attn : last_gain;
-        enqueue_layer(ctx, &layers[l], ctx->x, &kv[l], ctx_len, next_gain, l + 1 < layer_end, st);
+        const bool last = l + 1 == layer_end;
+        enqueue_layer(ctx, &layers[l], ctx->x, &kv[l], ctx_len, last ? last_gain : layers[l + 1].g_attn, !last, st,
+                      last ? x_out : nullptr);
     }
+    return x_out != nullptr;
 }
 
 static int check_layer_range(const cats_ctx* ctx, const cats_layer_weights* layers, int layer_begin,
@@ -913,13 +938,14 @@ int cats_verify_tree(cats_ctx* ctx, const cats_layer_weights* layers, int32_t la
     if (!g_final || !w_lm || !out_dev) return CATS_EINVAL;
     hipStream_t st = as_stream(stream);
     const int T = ctx->T, H = ctx->d.hidden;
-    enqueue_rows_and_layers(ctx, layers, layer_begin, layer_end, embed, hidden_in, g_final, kv, ctx_len, st);
-    if (hidden_out && T > 1)
+    const bool direct = enqueue_rows_and_layers(ctx, layers, layer_begin, layer_end, embed, hidden_in, g_final, kv,
+                                                ctx_len, hidden_out, st);
+    if (hidden_out && !direct && T > 1)
         HIP_TRY(hipMemcpyAsync(hidden_out, ctx->x, sizeof(float) * T * H, hipMemcpyDeviceToDevice, st));
     int32_t* amax = argmax_out ? argmax_out : ctx->amax;
     const bool typical = ctx->accept_mode == 1;
-    enqueue_lm_head(ctx, w_lm, logits_out, amax, margin_out, st, typical);
-    if (hidden_out && T == 1)   // a single row is final only once the LM head's product has updated it
+    enqueue_lm_head(ctx, w_lm, logits_out, amax, margin_out, st, typical, direct && T == 1 ? hidden_out : nullptr);
+    if (hidden_out && !direct && T == 1)   // a single row is final only once the LM head's product has updated it
         HIP_TRY(hipMemcpyAsync(hidden_out, ctx->row.x, sizeof(float) * H, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipGetLastError());
     return enqueue_accept_compact(ctx, amax, kv, layer_begin, layer_end, ctx_len, out_dev, out_host, st,
@@ -958,7 +984,8 @@ int cats_compact_along(cats_ctx* ctx, const cats_accept_result* result_dev, cons
     if (!result_dev || layer_begin < 0 || layer_end < layer_begin || layer_end > ctx->d.n_layers)
         return CATS_EINVAL;
     if (layer_end > layer_begin && !kv_ok(kv, layer_begin, layer_end)) return CATS_EINVAL;
-    enqueue_compact(ctx, kv, layer_begin, layer_end, ctx_len, result_dev, as_stream(stream));
+    if (layer_end > layer_begin)
+        launch_compact(compact_args(ctx, kv, layer_begin, layer_end, ctx_len, result_dev), as_stream(stream));
     HIP_TRY(hipGetLastError());
     return CATS_OK;
 }
@@ -974,9 +1001,11 @@ int cats_verify_nodes(cats_ctx* ctx, const cats_layer_weights* layers, int32_t l
     hipStream_t st = as_stream(stream);
     ctx->n0 = node_begin;   // read by the enqueue helpers
     ctx->rows = ctx->T - node_begin;
-    enqueue_rows_and_layers(ctx, layers, layer_begin, layer_end, embed, hidden_in, nullptr, kv, ctx_len, st);
-    const size_t bytes = sizeof(float) * static_cast<size_t>(ctx->T - node_begin) * ctx->d.hidden;
-    HIP_TRY(hipMemcpyAsync(hidden_out, ctx->x, bytes, hipMemcpyDeviceToDevice, st));
+    if (!enqueue_rows_and_layers(ctx, layers, layer_begin, layer_end, embed, hidden_in, nullptr, kv, ctx_len, hidden_out,
+                                 st)) {
+        const size_t bytes = sizeof(float) * static_cast<size_t>(ctx->T - node_begin) * ctx->d.hidden;
+        HIP_TRY(hipMemcpyAsync(hidden_out, ctx->x, bytes, hipMemcpyDeviceToDevice, st));
+    }
     HIP_TRY(hipGetLastError());
     return CATS_OK;
 }
@@ -1006,10 +1035,9 @@ int cats_draft_chain(cats_ctx* ctx, const cats_layer_weights* layers, int32_t la
         ctx->h_parent[i] = i - 1;
         ctx->h_depth[i] = i;
     }
-    launch_tree_upload(up, n, ctx->token, ctx->parent, ctx->depth, st);
-    launch_tree_masks(ctx->parent, n, ctx->anc, st);
+    launch_tree_upload(up, n, ctx->token, ctx->parent, ctx->depth, ctx->anc, st);
     ctx->T = n;
-    enqueue_rope_table(ctx, ctx_len, st);
+    launch_rope_table(rope_table_args(ctx, ctx_len), st);
     const size_t H = ctx->d.hidden;
     for (int k = 0; k <= gamma; ++k) {
         if (k == gamma && !hidden_out) break;   // the last draft only needs its hidden state
@@ -1186,7 +1214,6 @@ int cats_verify_tree_streamed(cats_ctx* ctx, const cats_layer_weights* host_laye
     int erc = enqueue_copy(layer_begin, false);
     if (erc != CATS_OK) return erc;
 
-    enqueue_rope_table(ctx, ctx_len, st);
     ResidualNormArgs rn;
     rn.x = ctx->x;
     rn.x_in = hidden_in;
@@ -1201,7 +1228,7 @@ int cats_verify_tree_streamed(cats_ctx* ctx, const cats_layer_weights* host_laye
     rn.T = T;
     rn.H = ctx->d.hidden;
     rn.eps = ctx->d.rms_eps;
-    launch_residual_norm(rn, st);
+    launch_rows_begin(rn, rope_table_args(ctx, ctx_len), st);
     rn.x_in = nullptr;
     rn.embed = nullptr;
     for (int l = layer_begin; l < layer_end; ++l) {
@@ -1328,7 +1355,6 @@ int cats_tree_attention_noalloc(const void* q, const cats_kv_layer* kv, const in
     const size_t o_po = take(slots * head_dim * sizeof(float));
     if (off > CATS_NOALLOC_SCRATCH_BYTES) return CATS_ECAPACITY;
     unsigned char* b = dev->ptr;
-    int32_t* d_parent = reinterpret_cast<int32_t*>(b + o_par);
     a.anc = reinterpret_cast<u32x4*>(b + o_anc);
     a.pml = reinterpret_cast<float*>(b + o_pml);
     a.po = reinterpret_cast<float*>(b + o_po);
@@ -1336,9 +1362,8 @@ int cats_tree_attention_noalloc(const void* q, const cats_kv_layer* kv, const in
     hipStream_t st = as_stream(stream);
     // the array keeps whatever the last call left: the arrival counters must start at zero
     launch_zero_i32(a.arrivals, n_counters, st);
-    launch_tree_upload(up, n_nodes, reinterpret_cast<int32_t*>(b + o_tok), d_parent,
-                       reinterpret_cast<int32_t*>(b + o_dep), st);
-    launch_tree_masks(d_parent, n_nodes, reinterpret_cast<u32x4*>(b + o_anc), st);
+    launch_tree_upload(up, n_nodes, reinterpret_cast<int32_t*>(b + o_tok), reinterpret_cast<int32_t*>(b + o_par),
+                       reinterpret_cast<int32_t*>(b + o_dep), reinterpret_cast<u32x4*>(b + o_anc), st);
     launch_attention(a, st);
     HIP_TRY(hipGetLastError());
     return CATS_OK;

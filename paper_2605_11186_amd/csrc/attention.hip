@@ -3,7 +3,7 @@
 //
 // Node i attends to cache rows [0, ctx_len) and to rows ctx_len + a for every a
 // on its root-to-node path.  The ancestor sets are 128-bit masks, built from parent[] in
-// LDS by cats_tree_masks when the tree is uploaded and read here one mask per query.
+// LDS by cats_tree_upload when the tree is set and read here one mask per query.
 //
 // Work split: one workgroup of W waves per (head, chunk of key blocks, group of
 // ATTN_QN queries); wave w takes the chunk's blocks w, w + W, ... and the waves'
@@ -684,25 +684,6 @@ __global__ __launch_bounds__(256) void cats_decode_attention(DecodeAttnArgs a) {
     }
 }
 
-// Ancestor-or-self set of every node as a 128-bit mask (bit a of anc[i] set when a is on the
-// path root..i): the tree attention mask in compact form.  One workgroup, parent[] in LDS.
-__global__ __launch_bounds__(CATS_MAX_TREE) void cats_tree_masks(const int32_t* parent, int T, u32x4* anc) {
-    __shared__ int32_t s_parent[CATS_MAX_TREE];
-    const int i = threadIdx.x;
-    if (i < T) s_parent[i] = parent[i];
-    __syncthreads();
-    if (i >= T) return;
-    u32x4 mask = u32x4{0u, 0u, 0u, 0u};
-    int node = i;
-    for (int step = 0; step <= CATS_MAX_DEPTH && node >= 0; ++step) {
-        const uint32_t bit = 1u << (node & 31);
-        const int w = node >> 5;
-        mask |= u32x4{w == 0 ? bit : 0u, w == 1 ? bit : 0u, w == 2 ? bit : 0u, w == 3 ? bit : 0u};
-        node = s_parent[node];
-    }
-    anc[i] = mask;
-}
-
 __global__ void cats_zero_i32(int* p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
@@ -712,10 +693,6 @@ __global__ void cats_zero_i32(int* p, int n) {
 
 void launch_zero_i32(int* p, int n, hipStream_t st) {
     hipLaunchKernelGGL(cats_zero_i32, dim3((n + 255) / 256), dim3(256), 0, st, p, n);
-}
-
-void launch_tree_masks(const int32_t* parent, int T, u32x4* anc, hipStream_t st) {
-    hipLaunchKernelGGL(cats_tree_masks, dim3(1), dim3(CATS_MAX_TREE), 0, st, parent, T, anc);
 }
 
 void launch_decode_attention(const DecodeAttnArgs& a, hipStream_t st) {

@@ -250,6 +250,7 @@ __device__ __forceinline__ f32x4 join_bf4(uint2 hi, uint2 lo) {
 
 struct ResidualNormArgs {
     float* x;               // [T][H] residual stream, in/out
+    float* x_out = nullptr; // if given, the updated rows go here instead of back to x (16-byte aligned)
     const float* x_in;      // optional [T][H]: start from this instead of x
     const bf16_t* embed;    // optional [V][H]: start from embed[token[t]]
     const int32_t* token;   // device [T]
@@ -272,6 +273,9 @@ struct RopeTableArgs {
     float base;
 };
 void launch_rope_table(const RopeTableArgs& a, hipStream_t st);
+// The first launch of a call: its rows and their norm input (no partial sums to add) and, by further
+// workgroups of the same launch, the rotation table
+void launch_rows_begin(const ResidualNormArgs& a, const RopeTableArgs& r, hipStream_t st);
 
 struct QkvRopeArgs {
     const float* part;  // [pieces][T][3H]: q | k | v, still to be scaled by the row's norm factor
@@ -434,7 +438,7 @@ struct AttnArgs {
     const bf16_t* k_lo;     // optional [nh][TREE_WIN][d] low parts of key rows lo_begin .. lo_end - 1
     const bf16_t* vt_lo;    // optional [nh][d][TREE_WIN]
     int lo_begin, lo_end;   // cache rows that have low parts (empty range: none)
-    const u32x4* anc;       // device [T] ancestor-or-self masks (cats_tree_masks)
+    const u32x4* anc;       // device [T] ancestor-or-self masks (cats_tree_upload)
     int T, H, nh, d, max_ctx, ctx_len;   // T: tree nodes whose K/V rows ctx_len.. take part as keys
     int Tq, q0;             // the queries are nodes q0 .. q0+Tq-1 (rows 0..Tq-1 of q / out)
     int n_chunks, t_pad;    // key chunks per (head, query group); rows per (head, chunk) in po / pml
@@ -473,7 +477,6 @@ struct DecodeAttnArgs {
     float* pml;          // [nh][n_chunks][2]  running maximum (base 2) and row sum of the chunk
 };
 void launch_decode_attention(const DecodeAttnArgs& a, hipStream_t st);
-void launch_tree_masks(const int32_t* parent, int T, u32x4* anc, hipStream_t st);
 void launch_attention(const AttnArgs& a, hipStream_t st);
 void launch_zero_i32(int* p, int n, hipStream_t st);   // fill kernel (a memset node must not enter a captured graph)
 
@@ -482,11 +485,16 @@ struct TreeUploadArgs {
     int32_t token[CATS_MAX_TREE], parent[CATS_MAX_TREE], depth[CATS_MAX_TREE];
 };
 void launch_tree_upload(const TreeUploadArgs& a, int n, int32_t* token, int32_t* parent,
-                        int32_t* depth, hipStream_t st);
+                        int32_t* depth, u32x4* anc, hipStream_t st);
 
-void launch_accept(const int32_t* token, const int32_t* parent, const int32_t* depth,
-                   const int32_t* amax, const uint8_t* edge_ok, int T, int ctx_len,
-                   cats_accept_result* out, hipStream_t st);
+struct AcceptArgs {
+    const int32_t *token, *parent, *depth;   // device [T]
+    const int32_t* amax;      // [T] the target's greedy token at every node
+    const uint8_t* edge_ok;   // optional [T], see cats_accept
+    int T, ctx_len;
+    cats_accept_result* out;
+};
+void launch_accept(const AcceptArgs& a, hipStream_t st);
 
 struct TypicalArgs {
     const int32_t* token;
@@ -509,6 +517,7 @@ struct CompactArgs {
     bf16_t* v[CATS_MAX_LAYERS];
     int n_layers;  // entries used
     int nh, d, max_ctx, ctx_len;
-    const cats_accept_result* res;
+    const cats_accept_result* res;   // cats_kv_compact: the path to roll back along
 };
 void launch_compact(const CompactArgs& a, hipStream_t st);
+void launch_accept_compact(const AcceptArgs& w, const CompactArgs& a, hipStream_t st);

@@ -11,17 +11,7 @@ namespace {
 // high + low bf16 parts;  ss[t][block] = sum of x^2 over the block's columns.  One wave per
 // (row, block of 256 columns): nothing here needs a whole row, so the launch has T * H/256
 // independent waves.
-__global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualNormArgs a) {
-    int t = blockIdx.x, blk = blockIdx.y;
-    if (a.xp) {
-        // Packed X: a 128-byte line holds 16 bytes of each of eight rows.  The 16 rows of a block of
-        // columns run on one XCD (workgroup b runs on XCD b % 8), so that its L2 collects the whole line.
-        const int n_blk = (a.H + SS_COLS - 1) / SS_COLS;
-        const int pair = blockIdx.x / 128 * 8 + blockIdx.x % 8;   // (row group, block of columns)
-        blk = pair % n_blk;
-        t = pair / n_blk * 16 + blockIdx.x / 8 % 16;
-        if (t >= a.T) return;
-    }
+__device__ __forceinline__ void residual_norm_block(const ResidualNormArgs& a, int t, int blk) {
     const int j = blk * SS_COLS + 4 * threadIdx.x;
     float ss = 0.f;
     if (j < a.H) {
@@ -38,7 +28,7 @@ __global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualNormArgs a) 
             val += sum_pieces4<16>(a.part + row + j, static_cast<size_t>(a.T) * a.H, plan_pieces(a.plan, j / a.plan.bn));
         }
         ss = sum_squares4(val);
-        if (a.embed || a.x_in || a.part) *reinterpret_cast<f32x4*>(a.x + row + j) = val;
+        if (a.embed || a.x_in || a.part) *reinterpret_cast<f32x4*>((a.x_out ? a.x_out : a.x) + row + j) = val;
         if (a.gain) {
             uint2 hi, lo;
             gain_split4(val, *reinterpret_cast<const uint2*>(a.gain + j), hi, lo);
@@ -52,17 +42,43 @@ __global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualNormArgs a) 
     ss = wave_sum64(ss);
     if (threadIdx.x == 0) a.ss[t * SS_STRIDE + blk] = ss;
 }
+// Packed X: a 128-byte line holds 16 bytes of each of eight rows.  The 16 rows of a block of
+// columns run on one XCD (workgroup b runs on XCD b % 8), so that its L2 collects the whole line.
+__device__ __forceinline__ void packed_row_block(const ResidualNormArgs& a, int b, int& t, int& blk) {
+    const int n_blk = (a.H + SS_COLS - 1) / SS_COLS;
+    const int pair = b / 128 * 8 + b % 8;   // (row group, block of columns)
+    blk = pair % n_blk;
+    t = pair / n_blk * 16 + b / 8 % 16;
+}
+__global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualNormArgs a) {
+    int t = blockIdx.x, blk = blockIdx.y;
+    if (a.xp) packed_row_block(a, blockIdx.x, t, blk);
+    if (t < a.T) residual_norm_block(a, t, blk);
+}
 
 // cos/sin of pos * base^(-2j/d) for pos = ctx_len + depth[t]; computed in double so
 // that the angle carries no float rounding of a four-digit position.
-__global__ void cats_rope_table(RopeTableArgs a) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void rope_entry(const RopeTableArgs& a, int idx) {
     const int half = a.d / 2;
     if (idx >= a.T * half) return;
     const int t = idx / half, j = idx - t * half;
     const double inv_freq = pow(static_cast<double>(a.base), -2.0 * j / a.d);
     const double ang = static_cast<double>(a.ctx_len + a.depth[t]) * inv_freq;
     a.cs[idx] = make_float2(static_cast<float>(cos(ang)), static_cast<float>(sin(ang)));
+}
+__global__ void cats_rope_table(RopeTableArgs a) { rope_entry(a, blockIdx.x * blockDim.x + threadIdx.x); }
+
+// The first launch of a call.  Its two halves do not depend on each other and are bound by launch latency: the rotation
+// table's workgroups (the longer ones) come first, a multiple of eight of them so that the rows' keep their XCDs.
+__global__ __launch_bounds__(64) void cats_rows_begin(ResidualNormArgs a, RopeTableArgs r, int rope_blocks) {
+    const int b = static_cast<int>(blockIdx.x) - rope_blocks;
+    if (b < 0) {
+        rope_entry(r, blockIdx.x * 64 + threadIdx.x);
+        return;
+    }
+    int t = b % a.T, blk = b / a.T;
+    if (a.xp) packed_row_block(a, b, t, blk);
+    if (t < a.T) residual_norm_block(a, t, blk);
 }
 
 // Adds up q|k|v partials, scales by the row's norm factor, rotates q and k (pairs j, j+d/2),
@@ -351,11 +367,20 @@ __global__ __launch_bounds__(AM_THREADS) void cats_argmax(ArgmaxArgs a) {
 
 }  // namespace
 
+static int packed_row_blocks(const ResidualNormArgs& a) {   // workgroups that packed_row_block deals out
+    const int pairs = (a.T + 15) / 16 * ((a.H + SS_COLS - 1) / SS_COLS);
+    return (pairs + 7) / 8 * 128;
+}
+
 void launch_residual_norm(const ResidualNormArgs& a, hipStream_t st) {
-    const int n_blk = (a.H + SS_COLS - 1) / SS_COLS;
-    const int pairs = (a.T + 15) / 16 * n_blk;   // packed X: see the kernel
-    const dim3 grid = a.xp ? dim3((pairs + 7) / 8 * 128) : dim3(a.T, n_blk);
+    const dim3 grid = a.xp ? dim3(packed_row_blocks(a)) : dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS);
     hipLaunchKernelGGL(cats_residual_rmsnorm, grid, dim3(64), 0, st, a);
+}
+
+void launch_rows_begin(const ResidualNormArgs& a, const RopeTableArgs& r, hipStream_t st) {
+    const int rows = a.xp ? packed_row_blocks(a) : a.T * ((a.H + SS_COLS - 1) / SS_COLS);
+    const int rope = (r.T * (r.d / 2) + 511) / 512 * 8;
+    hipLaunchKernelGGL(cats_rows_begin, dim3(rope + rows), dim3(64), 0, st, a, r, rope);
 }
 
 void launch_rope_table(const RopeTableArgs& a, hipStream_t st) {

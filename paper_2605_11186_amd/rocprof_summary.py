@@ -10,7 +10,7 @@ one with `--pmc FETCH_SIZE` and one with `--pmc WRITE_SIZE` (`--output-format cs
 counters by what they read for a plain copy kernel of known size in the same run
 (`bench.py --calibrate-copy`: one 1 GiB device-to-device copy) and prints the HBM bytes per
 dispatch for every kernel, per launch of the weight-streaming products (mean over the dispatches of
-all `cats_gemm*` kernels), and per verify step (all `cats_*` kernels of one step; steps are counted by the one `cats_accept` dispatch each has).
+all `cats_gemm*` kernels), and per verify step (all `cats_*` kernels of one step; steps are counted by the one `cats_accept` or `cats_accept_compact` dispatch each has).
 Nothing here touches a GPU: it only reads files.
 """
 from __future__ import annotations
@@ -28,6 +28,10 @@ def _short(name: str) -> str:
     return re.sub(r"\(anonymous namespace\)::", "", name)
 
 
+def _is_accept(name: str) -> bool:
+    return "cats_accept(" in name or "cats_accept_compact(" in name
+
+
 def kernel_trace(db_path: str) -> str:
     con = sqlite3.connect(db_path)
     rows = con.execute("select name, count(*), sum(end-start), avg(end-start), min(end-start), max(end-start) "
@@ -38,7 +42,7 @@ def kernel_trace(db_path: str) -> str:
         out.append(f"{_short(name)[:72]:72s} {calls:6d} {tot / 1e6:10.3f} {avg / 1e3:9.2f} {mn / 1e3:9.2f} "
                    f"{mx / 1e3:9.2f} {100 * tot / total:6.2f}")
     out.append(f"total kernel time {total / 1e6:.3f} ms")
-    steps = sum(r[1] for r in rows if "cats_accept(" in r[0])
+    steps = sum(r[1] for r in rows if _is_accept(r[0]))
     if steps:
         step_ns = sum(r[2] for r in rows if "cats_" in r[0] and "pack_matrix" not in r[0])
         out.append(f"{steps} verify steps in the trace; kernel time of the step's own kernels (cats_*, without the "
@@ -62,7 +66,7 @@ def traffic(fetch_csv: str, write_csv: str) -> str:
     f_copy, w_copy = max(fetch[copy[0]]), max(write[copy[0]])
     f_scale, w_scale = COPY_KIB / f_copy, COPY_KIB / w_copy
     mean = lambda v: sum(v) / len(v) if v else 0.0
-    steps = len(fetch.get(next((k for k in fetch if "cats_accept(" in k), ""), []))
+    steps = sum(len(v) for k, v in fetch.items() if _is_accept(k))
     out = ["calibration: one 1 GiB device-to-device copy (reads 1048576 KiB, writes 1048576 KiB)",
            f"  copy kernel {copy[0]}: FETCH_SIZE = {f_copy:.1f}, WRITE_SIZE = {w_copy:.1f}",
            f"  => scale factors: fetch x{f_scale:.4f}, write x{w_scale:.4f} (counter units -> KiB)",
