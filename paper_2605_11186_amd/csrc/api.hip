@@ -102,7 +102,7 @@ int target_wgs(const cats_ctx* c) { return c->n_cus; }
 // about one per compute unit; more chunks than that only add hand-over traffic between workgroups.
 int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_keys) {
     const int n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
-    const int groups = (rows + ATTN_QN - 1) / ATTN_QN;
+    const int groups = (rows + attn_queries(rows) - 1) / attn_queries(rows);
     const int chunks = std::max(1, n_cus / std::max(1, n_heads * groups));
     return std::min(chunks, std::min(n_blocks, max_chunks));
 }
@@ -1348,7 +1348,7 @@ int cats_tree_attention_noalloc(const void* q, const cats_kv_layer* kv, const in
     };
     const size_t o_tok = take(CATS_MAX_TREE * 4), o_par = take(CATS_MAX_TREE * 4), o_dep = take(CATS_MAX_TREE * 4);
     const size_t o_anc = take(CATS_MAX_TREE * sizeof(u32x4));
-    const int n_counters = n_heads * ((n_nodes + ATTN_QN - 1) / ATTN_QN);
+    const int n_counters = n_heads * ((n_nodes + attn_queries(n_nodes) - 1) / attn_queries(n_nodes));
     const size_t o_arr = take(static_cast<size_t>(n_counters) * sizeof(int));
     const size_t slots = static_cast<size_t>(n_heads) * a.n_chunks * a.t_pad;
     const size_t o_pml = take(slots * 2 * sizeof(float));

@@ -6,7 +6,7 @@
 // LDS by cats_tree_upload when the tree is set and read here one mask per query.
 //
 // Work split: one workgroup of W waves per (head, chunk of key blocks, group of
-// ATTN_QN queries); wave w takes the chunk's blocks w, w + W, ... and the waves'
+// 16 or 32 queries, see attn_queries); wave w takes the chunk's blocks w, w + W, ... and the waves'
 // partial results are merged through LDS.  With more than one chunk the workgroup then
 // publishes its chunk's result, and the last workgroup of a (head, query group) to arrive adds
 // up all chunks in chunk order with the usual log-sum-exp rescaling and writes the output:
@@ -180,32 +180,44 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         for (int db = 0; db < DB; ++db)
             v[db] = as_bf16x8(keep_keys(__builtin_bit_cast(u32x4, v[db]), blk * ATTN_KB + 8 * q4, 0, n_keys));
     };
-    auto load_k_lo = [&](bf16x8 (&kf)[2][KS], int blk) {
+    auto request_k_lo = [&](bf16x8 (&kf)[2][KS], int blk) {
         const bf16_t* kl = a.k_lo + static_cast<size_t>(h) * TREE_WIN * D;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const int key = blk * ATTN_KB + 8 * (m >> 2) + 4 * b + (m & 3);
-            const bool ok = key >= a.lo_begin && key < a.lo_end;
             const int w = min(key - win_base, TREE_WIN - 1);
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const u32x4 v = *reinterpret_cast<const u32x4*>(kl + static_cast<size_t>(w) * D + 32 * s + 8 * q4);
-                kf[b][s] = as_bf16x8(ok ? v : u32x4{0u, 0u, 0u, 0u});
-            }
+            for (int s = 0; s < KS; ++s)
+                kf[b][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(kl + static_cast<size_t>(w) * D + 32 * s + 8 * q4));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto keep_k_lo = [&](bf16x8 (&kf)[2][KS], int blk) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int key = blk * ATTN_KB + 8 * (m >> 2) + 4 * b + (m & 3);
+            const bool ok = key >= a.lo_begin && key < a.lo_end;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                kf[b][s] = as_bf16x8(ok ? __builtin_bit_cast(u32x4, kf[b][s]) : u32x4{0u, 0u, 0u, 0u});
         }
     };
-    auto load_v_lo = [&](bf16x8 (&vf)[DB], int blk) {
+    auto request_v_lo = [&](bf16x8 (&vf)[DB], int blk) {
         // (the window of a head is small: 32-bit offsets where registers are short)
         const bf16_t* vl = a.vt_lo + static_cast<size_t>(h) * D * TREE_WIN;
         const int key0 = blk * ATTN_KB + 8 * q4;
         const int w0 = min(key0 - win_base, TREE_WIN - 8);
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(
+        for (int db = 0; db < DB; ++db)
+            vf[db] = as_bf16x8(*reinterpret_cast<const u32x4*>(
                 D == 128 ? vl + static_cast<uint32_t>((16 * db + m) * TREE_WIN + w0)
-                         : vl + static_cast<size_t>(16 * db + m) * TREE_WIN + w0);
-            vf[db] = as_bf16x8(keep_keys(v, key0, a.lo_begin, a.lo_end));
-        }
+                         : vl + static_cast<size_t>(16 * db + m) * TREE_WIN + w0));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto keep_v_lo = [&](bf16x8 (&vf)[DB], int blk) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+            vf[db] = as_bf16x8(keep_keys(__builtin_bit_cast(u32x4, vf[db]), blk * ATTN_KB + 8 * q4, a.lo_begin, a.lo_end));
     };
 
     // MODE 0: every key of the block is a context row (no mask, no tail: straight-line code);
@@ -323,15 +335,23 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // the costlier blocks first: their loads go out with the kernel's first requests
     if (have_lo) {
         for (int blk = my_first(lo_blk); blk < blk_end; blk += blk_stride) {
+            bf16x8 vl[DB];
             {
                 bf16x8 kl[2][KS];
                 load_k(kf, blk);
-                load_k_lo(kl, blk);
+                request_k_lo(kl, blk);
+                if constexpr (QB == 1) {   // registers for all of the block: one memory round trip instead of two
+                    load_v(vf, blk);
+                    request_v_lo(vl, blk);
+                }
+                keep_k_lo(kl, blk);
                 scores(kf, kl, std::true_type{});
             }
-            bf16x8 vl[DB];
-            load_v(vf, blk);
-            load_v_lo(vl, blk);
+            if constexpr (QB > 1) {
+                load_v(vf, blk);
+                request_v_lo(vl, blk);
+            }
+            keep_v_lo(vl, blk);
             mask_v(vf, blk);
             weigh(vf, vl, blk, std::integral_constant<int, 2>{});
         }
@@ -376,33 +396,34 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // ... and the workgroup merges them (fixed wave order) into the chunk's result.
     // thread -> (query ql, dims 4 (i TPQ + c) .. + 3 for i < NI): the TPQ threads of a query cover
     // 4 TPQ consecutive dims per i, so every 16-byte access of a wave falls into whole 128-byte lines
-    constexpr int TPQ = 64 * W / QN;      // threads per query
+    constexpr int TPQ = 64 * W / QN < D / 4 ? 64 * W / QN : D / 4;   // threads per query (any others are done)
     constexpr int NI = D / (4 * TPQ);
     static_assert(NI >= 1 && NI * 4 * TPQ == D, "merge mapping");
     const int ql = threadIdx.x / TPQ, c4 = 4 * (threadIdx.x % TPQ);
-    float M = -1e30f;
-#pragma unroll
-    for (int w = 0; w < W; ++w) M = fmaxf(M, s_ml[w][ql][0]);
-    float wgt[W], l = 0.f;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        wgt[w] = __builtin_amdgcn_exp2f(s_ml[w][ql][0] - M);
-        l += wgt[w] * s_ml[w][ql][1];
-    }
+    const bool mine = ql < QN && qbase + ql < Tq;   // rows that hold no query are left out
+    float M = -1e30f, l = 0.f;
     f32x4 acc[NI];
+    if (mine) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < W; ++w) M = fmaxf(M, s_ml[w][ql][0]);
+        float wgt[W];
 #pragma unroll
-        for (int w = 0; w < W; ++w) acc[i] += wgt[w] * *reinterpret_cast<const f32x4*>(&s_o[w][ql][4 * TPQ * i + c4]);
+        for (int w = 0; w < W; ++w) {
+            wgt[w] = __builtin_amdgcn_exp2f(s_ml[w][ql][0] - M);
+            l += wgt[w] * s_ml[w][ql][1];
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < W; ++w) acc[i] += wgt[w] * *reinterpret_cast<const f32x4*>(&s_o[w][ql][4 * TPQ * i + c4]);
+        }
     }
 
     // out[t][h*D + dims] = num / den as high (+ low) bf16 parts
     auto write_out = [&](const f32x4 (&num)[NI], float den) {
-        const int t = qbase + ql;
-        if (t >= Tq) return;
         const float inv = 1.0f / den;
-        const size_t o_off = static_cast<size_t>(t) * a.H + h * D + c4;
+        const size_t o_off = static_cast<size_t>(qbase + ql) * a.H + h * D + c4;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             uint2 hi, lo;
@@ -413,15 +434,15 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         }
     };
     if (a.n_chunks == 1) {
-        write_out(acc, l);
+        if (mine) write_out(acc, l);
         return;
     }
 
     // Publish this chunk.  The values move with device-coherent stores and loads (sc1: they
     // bypass the per-XCD caches) in whole 128-byte lines; waiting for the stores' acknowledgement
     // before the arrival count is raised orders them without a cache write-back / invalidate.
-    const size_t slot = (static_cast<size_t>(h) * a.n_chunks + chunk) * a.t_pad + qbase + ql;
-    {
+    if (mine) {
+        const size_t slot = (static_cast<size_t>(h) * a.n_chunks + chunk) * a.t_pad + qbase + ql;
         float* po = a.po + slot * D + c4;
 #pragma unroll
         for (int i = 0; i < NI; ++i) store_coherent16(po + 4 * TPQ * i, acc[i]);
@@ -437,9 +458,13 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         s_last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.n_chunks - 1;
     __syncthreads();
     if (!s_last) return;
+    if (threadIdx.x == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+    if (!mine) return;
     // last workgroup of this (head, query group): out = sum_c exp2(m_c - M) O_c / sum_c exp2(m_c - M) l_c,
     // chunks in index order, eight chunks' loads in flight at a time (one memory round trip for
-    // up to eight chunks), rescaled to the running maximum between groups
+    // up to eight chunks), rescaled to the running maximum between groups.  (Sharing this among the chunks'
+    // workgroups, each waiting for the others' arrivals, was slower: 16.7 against 12.6 us at 32 heads of 128, 32 nodes,
+    // 1024 rows.)
     constexpr int MG = 8;
     const float* po_head = a.po + static_cast<size_t>(h) * a.n_chunks * a.t_pad * D;
     const uint32_t po_bytes = static_cast<uint32_t>(a.n_chunks * a.t_pad) * D * 4;
@@ -480,7 +505,6 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         }
     }
     write_out(num, den);
-    if (threadIdx.x == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
 }
 
 // ---------------------------------------------------------------- single query
@@ -709,11 +733,23 @@ void launch_decode_attention(const DecodeAttnArgs& a, hipStream_t st) {
 // 1024 18.4 -> 17.3 -> 15.2, 63 / 4096 29.6 -> 29.8 -> 25.9, 128 / 4096 47.6 -> 46.6 -> 44.1; 8 heads, 16 nodes (32 chunks at 1024 rows and
 // more) / 512 rows 15.7 -> 13.9 -> 14.4, / 4096 21.5 -> 17.6 -> 19.0.  Head size 64 (no spill, half the LDS): eight, by 2.5 to 4 %.
 void launch_attention(const AttnArgs& a, hipStream_t st) {
-    const dim3 grid(a.n_chunks, a.nh, (a.Tq + ATTN_QN - 1) / ATTN_QN);
-    if (a.d == 64)
-        hipLaunchKernelGGL((cats_tree_attention_kernel<64, ATTN_QN / 16, 8>), grid, dim3(512), 0, st, a);
-    else if (a.n_chunks > 8)
-        hipLaunchKernelGGL((cats_tree_attention_kernel<128, ATTN_QN / 16, 8>), grid, dim3(512), 0, st, a);
-    else
-        hipLaunchKernelGGL((cats_tree_attention_kernel<128, ATTN_QN / 16, 4>), grid, dim3(256), 0, st, a);
+    const int qn = attn_queries(a.Tq);
+    const dim3 grid(a.n_chunks, a.nh, (a.Tq + qn - 1) / qn);
+#define CATS_ATTN(DV, QBV, WV) hipLaunchKernelGGL((cats_tree_attention_kernel<DV, QBV, WV>), grid, dim3(64 * WV), 0, st, a)
+    if (qn == 16) {
+        if (a.d == 64)
+            CATS_ATTN(64, 1, 8);
+        else if (a.n_chunks > 8)
+            CATS_ATTN(128, 1, 8);
+        else
+            CATS_ATTN(128, 1, 4);
+    } else {
+        if (a.d == 64)
+            CATS_ATTN(64, 2, 8);
+        else if (a.n_chunks > 8)
+            CATS_ATTN(128, 2, 8);
+        else
+            CATS_ATTN(128, 2, 4);
+    }
+#undef CATS_ATTN
 }

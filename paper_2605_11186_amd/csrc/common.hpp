@@ -430,6 +430,13 @@ void launch_gemv(const GemvArgs& a, hipStream_t st, hipEvent_t ev_start = nullpt
 // r - (ctx_len & ~31), i.e. the window starts at the 32-key block that holds row ctx_len, which
 // keeps 8-key vector loads 16-byte aligned.  Entries outside [lo_begin, lo_end) are stale.
 constexpr int TREE_WIN = 32 + CATS_MAX_TREE;   // rows of the window
+constexpr int ATTN_KB = 32;      // keys per block
+// Queries of a workgroup: up to 16 rows 16, else 32.  With one 16-query group a wave has half the arithmetic and half the
+// partial results to hand over, and registers to request all of a block with low parts at once.  Attention alone, 32 then 16
+// queries, us: 32 heads of 128, 2 nodes / 1024 rows 12.4 -> 9.0, 16 / 512 11.3 -> 8.2, 16 / 4096 20.5 -> 17.8; 4 heads of 64,
+// 15 / 128 6.6 -> 5.4.
+inline int attn_queries(int rows) { return rows <= 16 ? 16 : 32; }
+constexpr int ATTN_MAX_QGROUPS = CATS_MAX_TREE / 32;   // query groups per head at most
 struct AttnArgs {
     const bf16_t* q;        // [Tq][H]
     const bf16_t* q_lo;     // optional [Tq][H] low parts of q
@@ -448,11 +455,6 @@ struct AttnArgs {
     bf16_t* out;            // [Tq][H]
     bf16_t* out_lo;         // optional [Tq][H] low parts of the output
 };
-constexpr int ATTN_KB = 32;    // keys per block
-// An attention workgroup: four or eight waves (see launch_attention), each taking every fourth or eighth key
-// block of the workgroup's chunk for all ATTN_QN queries of the workgroup (two 16-query groups per wave).
-constexpr int ATTN_QN = 32;
-constexpr int ATTN_MAX_QGROUPS = CATS_MAX_TREE / ATTN_QN;   // query groups per head at most
 // Attention of a single-row call (one query node, T = 1 per step: the stage-1 draft loop, plain
 // decoding) with the q|k|v step folded in: every workgroup adds up the query columns of its head
 // from the q|k|v product's partial sums, scales and rotates them; the workgroup whose key chunk
