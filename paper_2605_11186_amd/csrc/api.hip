@@ -100,11 +100,25 @@ int target_wgs(const cats_ctx* c) { return c->n_cus; }
 
 // Key chunks per (head, query group): the launch has heads * query groups * chunks workgroups,
 // about one per compute unit; more chunks than that only add hand-over traffic between workgroups.
-int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_keys) {
+int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_keys, int queries) {
     const int n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
-    const int groups = (rows + attn_queries(rows) - 1) / attn_queries(rows);
+    const int groups = (rows + queries - 1) / queries;
     const int chunks = std::max(1, n_cus / std::max(1, n_heads * groups));
     return std::min(chunks, std::min(n_blocks, max_chunks));
+}
+// Queries of a workgroup.  With 16 a wave has half the arithmetic and half the partial results to hand over, and registers
+// to request all of a block with low parts at once; beyond 16 rows every 16 of them then read all keys and values, which is
+// the shorter way while a chunk has few key blocks (fewer where one chunk needs no hand-over with 16 but has all the keys).
+// In a layer, 32 then 16 queries, us (32 heads of 128; in brackets blocks a chunk, chunks): 20 nodes / 300 rows 11.7 -> 7.9,
+// 32 / 1024 (8, 4) 12.8 -> 10.5, 32 / 2000 (16, 4) 15.3 -> 14.0, 63 / 512 (9, 2) 12.6 -> 10.5, 33 / 1000 (17, 2) 13.5 -> 13.5,
+// 64 / 2048 (33, 2) 17.5 -> 21.9, 128 / 300 (14, 1) 16.1 -> 13.5, 128 / 512 (20, 1) 16.0 -> 16.0.  Attention alone: 40 heads,
+// 30 / 1500 (16, 3) 13.7 -> 14.6; 8 heads, 64 / 4096 (16, 8) 16.3 -> 14.0; 128 / 1024 (36, 1) 17.1 -> 20.1.
+void attn_split(AttnArgs& a, int n_cus, int max_chunks) {
+    const int n_keys = a.ctx_len + a.T, n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
+    const int narrow = attn_chunks(a.Tq, a.nh, max_chunks, n_cus, n_keys, 16);
+    a.queries = a.Tq <= 16 || n_blocks <= (narrow == 1 ? 14 : 18 * narrow - 8) ? 16 : 32;
+    a.n_chunks = a.queries == 16 ? narrow : attn_chunks(a.Tq, a.nh, max_chunks, n_cus, n_keys, 32);
+    a.t_pad = (a.Tq + 31) / 32 * 32;
 }
 
 hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
@@ -292,9 +306,7 @@ void enqueue_attention(cats_ctx* c, const bf16_t* q, const bf16_t* q_lo, const c
     a.d = c->d.head_dim;
     a.max_ctx = c->d.max_ctx;
     a.ctx_len = ctx_len;
-    const int n_keys = ctx_len + c->T;
-    a.n_chunks = attn_chunks(c->rows, c->d.n_heads, c->attn_max_chunks, c->n_cus, n_keys);
-    a.t_pad = (a.Tq + 31) / 32 * 32;
+    attn_split(a, c->n_cus, c->attn_max_chunks);
     a.po = c->attn_po;
     a.pml = c->attn_pml;
     a.out = out;
@@ -1335,10 +1347,7 @@ int cats_tree_attention_noalloc(const void* q, const cats_kv_layer* kv, const in
     a.d = head_dim;
     a.max_ctx = max_ctx;
     a.ctx_len = ctx_len;
-    const int n_keys = ctx_len + n_nodes;
-    const int n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
-    a.n_chunks = attn_chunks(n_nodes, n_heads, 32, dev->n_cus, n_keys);
-    a.t_pad = (n_nodes + 31) / 32 * 32;
+    attn_split(a, dev->n_cus, 32);
     // layout of the scratch array: tree arrays, ancestor masks, then the chunk partials
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1348,7 +1357,9 @@ int cats_tree_attention_noalloc(const void* q, const cats_kv_layer* kv, const in
     };
     const size_t o_tok = take(CATS_MAX_TREE * 4), o_par = take(CATS_MAX_TREE * 4), o_dep = take(CATS_MAX_TREE * 4);
     const size_t o_anc = take(CATS_MAX_TREE * sizeof(u32x4));
-    const int n_counters = n_heads * ((n_nodes + attn_queries(n_nodes) - 1) / attn_queries(n_nodes));
+    // (one chunk: the counters are not used; their place keeps the size that decides which shapes fit)
+    const int per_group = a.n_chunks > 1 ? a.queries : 32;
+    const int n_counters = n_heads * ((n_nodes + per_group - 1) / per_group);
     const size_t o_arr = take(static_cast<size_t>(n_counters) * sizeof(int));
     const size_t slots = static_cast<size_t>(n_heads) * a.n_chunks * a.t_pad;
     const size_t o_pml = take(slots * 2 * sizeof(float));

@@ -6,7 +6,7 @@
 // LDS by cats_tree_upload when the tree is set and read here one mask per query.
 //
 // Work split: one workgroup of W waves per (head, chunk of key blocks, group of
-// 16 or 32 queries, see attn_queries); wave w takes the chunk's blocks w, w + W, ... and the waves'
+// 16 or 32 queries, see attn_split); wave w takes the chunk's blocks w, w + W, ... and the waves'
 // partial results are merged through LDS.  With more than one chunk the workgroup then
 // publishes its chunk's result, and the last workgroup of a (head, query group) to arrive adds
 // up all chunks in chunk order with the usual log-sum-exp rescaling and writes the output:
@@ -733,7 +733,7 @@ void launch_decode_attention(const DecodeAttnArgs& a, hipStream_t st) {
 // 1024 18.4 -> 17.3 -> 15.2, 63 / 4096 29.6 -> 29.8 -> 25.9, 128 / 4096 47.6 -> 46.6 -> 44.1; 8 heads, 16 nodes (32 chunks at 1024 rows and
 // more) / 512 rows 15.7 -> 13.9 -> 14.4, / 4096 21.5 -> 17.6 -> 19.0.  Head size 64 (no spill, half the LDS): eight, by 2.5 to 4 %.
 void launch_attention(const AttnArgs& a, hipStream_t st) {
-    const int qn = attn_queries(a.Tq);
+    const int qn = a.queries;
     const dim3 grid(a.n_chunks, a.nh, (a.Tq + qn - 1) / qn);
 #define CATS_ATTN(DV, QBV, WV) hipLaunchKernelGGL((cats_tree_attention_kernel<DV, QBV, WV>), grid, dim3(64 * WV), 0, st, a)
     if (qn == 16) {

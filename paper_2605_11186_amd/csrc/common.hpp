@@ -431,12 +431,7 @@ void launch_gemv(const GemvArgs& a, hipStream_t st, hipEvent_t ev_start = nullpt
 // keeps 8-key vector loads 16-byte aligned.  Entries outside [lo_begin, lo_end) are stale.
 constexpr int TREE_WIN = 32 + CATS_MAX_TREE;   // rows of the window
 constexpr int ATTN_KB = 32;      // keys per block
-// Queries of a workgroup: up to 16 rows 16, else 32.  With one 16-query group a wave has half the arithmetic and half the
-// partial results to hand over, and registers to request all of a block with low parts at once.  Attention alone, 32 then 16
-// queries, us: 32 heads of 128, 2 nodes / 1024 rows 12.4 -> 9.0, 16 / 512 11.3 -> 8.2, 16 / 4096 20.5 -> 17.8; 4 heads of 64,
-// 15 / 128 6.6 -> 5.4.
-inline int attn_queries(int rows) { return rows <= 16 ? 16 : 32; }
-constexpr int ATTN_MAX_QGROUPS = CATS_MAX_TREE / 32;   // query groups per head at most
+constexpr int ATTN_MAX_QGROUPS = CATS_MAX_TREE / 16;   // query groups per head at most
 struct AttnArgs {
     const bf16_t* q;        // [Tq][H]
     const bf16_t* q_lo;     // optional [Tq][H] low parts of q
@@ -448,6 +443,7 @@ struct AttnArgs {
     const u32x4* anc;       // device [T] ancestor-or-self masks (cats_tree_upload)
     int T, H, nh, d, max_ctx, ctx_len;   // T: tree nodes whose K/V rows ctx_len.. take part as keys
     int Tq, q0;             // the queries are nodes q0 .. q0+Tq-1 (rows 0..Tq-1 of q / out)
+    int queries;            // of a workgroup: 16 or 32
     int n_chunks, t_pad;    // key chunks per (head, query group); rows per (head, chunk) in po / pml
     float* po;              // [nh][n_chunks][t_pad][d]
     float* pml;             // [nh][n_chunks][t_pad][2]

@@ -1,5 +1,5 @@
-"""Tree attention around the sizes where the queries of a workgroup change (16 rows | 17) and where padding rows
-begin and end, through whole layers (own rows with low parts) and alone, against float64 attention of the same inputs."""
+"""Tree attention around the sizes where the queries of a workgroup change (16 rows | 17, beyond that few | many key
+blocks a chunk) and where padding rows begin and end, through whole layers (own rows with low parts) and alone, against float64 attention of the same inputs."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("heads,d", [(4, 64), (3, 128), (40, 128)])
-@pytest.mark.parametrize("T,S", [(1, 0), (2, 31), (15, 33), (16, 512), (17, 95), (31, 700), (32, 64), (33, 1)])
+@pytest.mark.parametrize("T,S", [(1, 0), (2, 31), (15, 33), (16, 512), (17, 95), (31, 700), (32, 64), (33, 1), (64, 400), (65, 900), (128, 300),
+                                 (128, 513)])
 def test_alone(heads, d, T, S):
     gen = torch.Generator(device="cuda").manual_seed(T + S)
     H, max_ctx = heads * d, (S + T + 63) // 64 * 64
