@@ -333,9 +333,12 @@ int enqueue_row_attention(cats_ctx* c, const float* part, const GemmPlan& plan, 
     a.d = c->d.head_dim;
     a.max_ctx = c->d.max_ctx;
     a.ctx_len = ctx_len;
-    const int n_blocks = (ctx_len + c->n0 + 1 + ATTN_KB - 1) / ATTN_KB;
+    // (the node's own row comes beside the last chunk's keys)
+    const int n_blocks = std::max(1, (ctx_len + c->n0 + ATTN_KB - 1) / ATTN_KB);
     const int per_chunk = std::max(DEC_TILE / ATTN_KB, (n_blocks + DEC_MAX_CHUNKS - 1) / DEC_MAX_CHUNKS);
     a.n_chunks = (n_blocks + per_chunk - 1) / per_chunk;
+    // a last chunk of one block goes to the one before it where it would only make workgroups share compute units
+    if (a.n_chunks > 1 && n_blocks % per_chunk == 1 && a.n_chunks * a.nh > c->n_cus) --a.n_chunks;
     a.span = per_chunk * ATTN_KB;
     a.po = c->attn_po;
     a.pml = c->attn_pml;

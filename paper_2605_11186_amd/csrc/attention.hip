@@ -517,7 +517,30 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
 //   scores: a key row is D/8 16-byte pieces, one per lane, summed over those lanes;
 //   values: the cache is transposed, a dim's 128 keys are 16 16-byte pieces, one per lane.
 // Rows that must stay invisible (later siblings, rows past the tree, the node's own row, which is
-// being written meanwhile) are excluded by selects, never by a multiplication with zero.
+// being written meanwhile) are excluded by selects, never by a multiplication with zero; a tile of context rows alone
+// has none and goes without.
+// What bounds it: an empty launch takes 2.2 us, the memory round trip 3 and a wave's instructions 2 ns each, 7 of 10 us
+// with no key, value or partial sum loaded.  So: as few instructions as possible (no selects in full tiles, sums over 16
+// lanes on the vector ALU instead of shuffles through LDS) and not more workgroups than compute units where avoidable (the
+// node's own row is nobody's chunk: behind 1024 rows 32 heads have 256 workgroups, not 288).  32 heads of 128, launches in
+// a layer, us: 1024 rows 10.1 -> 6.7, 1024 + 1 to 5 nodes 9.7 -> 8.0; the output projection behind it, merging eight chunks
+// instead of nine, 9.9 -> 9.3.
+// sum over the N lanes (8 or 16, aligned) that lane belongs to, in all of them: rotations inside rows of 16 lanes (inside
+// half rows the exchange with lane ^ 4 is the half row mirrored and the quads mirrored back)
+template <int N>
+__device__ __forceinline__ float sum_lanes(float v) {
+    auto moved = [](float x, auto ctrl) {
+        return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    if constexpr (N == 16) v += moved(v, std::integral_constant<int, 0x128>{});   // row_ror:8
+    if constexpr (N == 16)
+        v += moved(v, std::integral_constant<int, 0x124>{});   // row_ror:4
+    else
+        v += moved(moved(v, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});   // row_half_mirror, quad 3 2 1 0
+    v += moved(v, std::integral_constant<int, 0x4E>{});   // quad_perm 2 3 0 1
+    v += moved(v, std::integral_constant<int, 0xB1>{});   // quad_perm 1 0 3 2
+    return v;
+}
 __device__ __forceinline__ bool mask_bit(const u32x4& m, int i) {
     const uint32_t w = i < 64 ? (i < 32 ? m[0] : m[1]) : (i < 96 ? m[2] : m[3]);
     return (w >> (i & 31)) & 1u;
@@ -539,14 +562,14 @@ __global__ __launch_bounds__(256) void cats_decode_attention(DecodeAttnArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int chunk = blockIdx.x, h = blockIdx.y;
     const int S = a.ctx_len, node = a.node;
-    const int n_keys = S + node + 1, own = S + node;
-    const int key_begin = chunk * a.span, key_end = min(key_begin + a.span, n_keys);
-    const bool owner = own >= key_begin && own < key_end;
+    const int own = S + node;   // the node's own row: the last chunk's, beside its keys
+    const bool owner = chunk == a.n_chunks - 1;
+    const int key_begin = chunk * a.span, key_end = owner ? own : key_begin + a.span;
     const u32x4 anc = a.anc[node];
     bf16_t* kbase = a.kc + static_cast<size_t>(h) * a.max_ctx * D;
     bf16_t* vbase = a.vt + static_cast<size_t>(h) * D * a.max_ctx;
     const float scale = rsqrtf(static_cast<float>(D)) * 1.44269504088896340736f;   // 1/sqrt(d) * log2(e)
-    auto visible = [&](int j) { return j < key_end && j != own && (j < S || mask_bit(anc, j - S)); };
+    auto visible = [&](int j) { return j < key_end && (j < S || mask_bit(anc, j - S)); };
 
     // requests: this wave's two columns of q, k or v (waves 0..2; k and v only where the node's
     // own row lives), then the first tile's keys and values
@@ -634,7 +657,9 @@ __global__ __launch_bounds__(256) void cats_decode_attention(DecodeAttnArgs a) {
 #pragma unroll
     for (int p = 0; p < VP; ++p) o_run[p] = 0.f;
     for (int t0 = key_begin;;) {
+        const bool full = t0 + DEC_TILE <= min(key_end, S);   // context rows alone (the same for the whole workgroup)
         // scores of the tile's keys
+        float sc[KP];
 #pragma unroll
         for (int p = 0; p < KP; ++p) {
             float dot = 0.f;
@@ -643,13 +668,17 @@ __global__ __launch_bounds__(256) void cats_decode_attention(DecodeAttnArgs a) {
                 dot = fmaf(__uint_as_float(kf[p][e] << 16), qs[2 * e], dot);
                 dot = fmaf(__uint_as_float(kf[p][e] & 0xFFFF0000u), qs[2 * e + 1], dot);
             }
-#pragma unroll
-            for (int o = LPK / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
-            const int kl = KPP * p + tid / LPK;
-            if (tid % LPK == 0) s_sc[kl] = visible(t0 + kl) ? dot * scale : -INFINITY;
+            sc[p] = sum_lanes<LPK>(dot) * scale;
         }
+        if (!full)
+#pragma unroll
+            for (int p = 0; p < KP; ++p)
+                if (!visible(t0 + KPP * p + tid / LPK)) sc[p] = -INFINITY;
+        if (tid % LPK == 0)
+#pragma unroll
+            for (int p = 0; p < KP; ++p) s_sc[KPP * p + tid / LPK] = sc[p];
         __syncthreads();
-        const bool own_here = owner && own >= t0 && own < t0 + DEC_TILE;
+        const bool own_here = owner && t0 + DEC_TILE >= key_end;   // with the last tile
         // tile maximum (every wave works it out for itself), this thread's 8 keys' weights, tile sum
         float m_t = fmaxf(s_sc[lane], s_sc[lane + 64]);
 #pragma unroll
@@ -662,26 +691,40 @@ __global__ __launch_bounds__(256) void cats_decode_attention(DecodeAttnArgs a) {
             pw[e] = __builtin_amdgcn_exp2f(s_sc[8 * (tid % 16) + e] - m_t);
             l_t += pw[e];
         }
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) l_t += __shfl_xor(l_t, o);
+        l_t = sum_lanes<16>(l_t);
         const float p_new = own_here ? __builtin_amdgcn_exp2f(s_new - m_t) : 0.f;
         l_t += p_new;
         // weighted values: 16 dims per pass, a dim's keys over 16 lanes
         const float m_new = fmaxf(m_run, m_t);
         const float c_run = __builtin_amdgcn_exp2f(m_run - m_new), c_t = __builtin_amdgcn_exp2f(m_t - m_new);
+        float acc[VP];
+        if (full) {
+#pragma unroll
+            for (int p = 0; p < VP; ++p) {
+                acc[p] = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[p] += pw[2 * e] * __uint_as_float(vf[p][e] << 16);
+                    acc[p] += pw[2 * e + 1] * __uint_as_float(vf[p][e] & 0xFFFF0000u);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < VP; ++p) {
+                acc[p] = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v0 = __uint_as_float(vf[p][e] << 16), v1 = __uint_as_float(vf[p][e] & 0xFFFF0000u);
+                    acc[p] += pw[2 * e] != 0.f ? pw[2 * e] * v0 : 0.f;
+                    acc[p] += pw[2 * e + 1] != 0.f ? pw[2 * e + 1] * v1 : 0.f;
+                }
+            }
+        }
 #pragma unroll
         for (int p = 0; p < VP; ++p) {
-            float acc = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v0 = __uint_as_float(vf[p][e] << 16), v1 = __uint_as_float(vf[p][e] & 0xFFFF0000u);
-                acc += pw[2 * e] != 0.f ? pw[2 * e] * v0 : 0.f;
-                acc += pw[2 * e + 1] != 0.f ? pw[2 * e + 1] * v1 : 0.f;
-            }
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-            if (own_here) acc += p_new * s_vn[16 * p + tid / 16];
-            o_run[p] = o_run[p] * c_run + acc * c_t;
+            acc[p] = sum_lanes<16>(acc[p]);
+            if (own_here) acc[p] += p_new * s_vn[16 * p + tid / 16];
+            o_run[p] = o_run[p] * c_run + acc[p] * c_t;
         }
         l_run = l_run * c_run + l_t * c_t;
         m_run = m_new;

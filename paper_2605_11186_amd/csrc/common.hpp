@@ -453,8 +453,8 @@ struct AttnArgs {
 };
 // Attention of a single-row call (one query node, T = 1 per step: the stage-1 draft loop, plain
 // decoding) with the q|k|v step folded in: every workgroup adds up the query columns of its head
-// from the q|k|v product's partial sums, scales and rotates them; the workgroup whose key chunk
-// holds the node's own cache row does the same for the key and value columns, appends them to the
+// from the q|k|v product's partial sums, scales and rotates them; the workgroup with the last key
+// chunk does the same for the node's own key and value columns, appends them to the
 // cache (bf16) and uses them (high + low part) without reading them back.  The kernel ends with
 // one partial result per (head, key chunk); the output projection that follows merges them while
 // it builds its input columns (GEMV_ATTN), so no workgroup waits for another.
@@ -470,7 +470,7 @@ struct DecodeAttnArgs {
     const u32x4* anc;    // ancestor-or-self masks of the uploaded tree
     int node;            // the query node; keys: rows [0, ctx_len) and ctx_len + j for j <= node on its path
     int H, nh, d, max_ctx, ctx_len;
-    int n_chunks, span;  // chunk c owns keys [c * span, (c + 1) * span); span is a multiple of 32
+    int n_chunks, span;  // chunk c owns keys [c * span, (c + 1) * span), the last one to the node's own row; span: a multiple of 32
     float* po;           // [nh][n_chunks][d]  unnormalised weighted value sums of the chunk
     float* pml;          // [nh][n_chunks][2]  running maximum (base 2) and row sum of the chunk
 };
