@@ -525,22 +525,6 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
 // node's own row is nobody's chunk: behind 1024 rows 32 heads have 256 workgroups, not 288).  32 heads of 128, launches in
 // a layer, us: 1024 rows 10.1 -> 6.7, 1024 + 1 to 5 nodes 9.7 -> 8.0; the output projection behind it, merging eight chunks
 // instead of nine, 9.9 -> 9.3.
-// sum over the N lanes (8 or 16, aligned) that lane belongs to, in all of them: rotations inside rows of 16 lanes (inside
-// half rows the exchange with lane ^ 4 is the half row mirrored and the quads mirrored back)
-template <int N>
-__device__ __forceinline__ float sum_lanes(float v) {
-    auto moved = [](float x, auto ctrl) {
-        return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, true));
-    };
-    if constexpr (N == 16) v += moved(v, std::integral_constant<int, 0x128>{});   // row_ror:8
-    if constexpr (N == 16)
-        v += moved(v, std::integral_constant<int, 0x124>{});   // row_ror:4
-    else
-        v += moved(moved(v, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});   // row_half_mirror, quad 3 2 1 0
-    v += moved(v, std::integral_constant<int, 0x4E>{});   // quad_perm 2 3 0 1
-    v += moved(v, std::integral_constant<int, 0xB1>{});   // quad_perm 1 0 3 2
-    return v;
-}
 __device__ __forceinline__ bool mask_bit(const u32x4& m, int i) {
     const uint32_t w = i < 64 ? (i < 32 ? m[0] : m[1]) : (i < 96 ? m[2] : m[3]);
     return (w >> (i & 31)) & 1u;

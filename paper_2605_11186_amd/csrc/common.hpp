@@ -206,11 +206,32 @@ __device__ __forceinline__ float row_scale(const NormScale& ns, const RowSquares
 }
 __device__ __forceinline__ float row_scale(const NormScale& ns, int t) { return row_scale(ns, row_squares_load(ns, t)); }
 
-__device__ __forceinline__ float wave_sum64(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// Sum over the N lanes (8, 16 or 64, aligned) that lane belongs to, in all of them: the butterfly v += v[lane ^ o] for
+// o = N/2 .. 1, every exchange on the vector ALU (a shuffle goes through LDS and costs about 120 cycles of a serial chain).
+template <int CTRL>
+__device__ __forceinline__ float dpp_moved(float x) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+template <int N>
+__device__ __forceinline__ float sum_lanes(float v) {
+    static_assert(N == 8 || N == 16 || N == 64, "lanes");
+    if constexpr (N == 64) {   // rows of 32, then of 16 lanes change places between two copies
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if constexpr (N >= 16) {
+        v += dpp_moved<0x128>(v);   // row_ror:8 is lane ^ 8
+        v += dpp_moved<0x124>(v);   // row_ror:4: lane ^ 4 where lanes i and i ^ 8 hold the same
+    } else {
+        v += dpp_moved<0x1B>(dpp_moved<0x141>(v));   // lane ^ 4: half rows mirrored, then quads 3 2 1 0
+    }
+    v += dpp_moved<0x4E>(v);   // quad_perm 2 3 0 1
+    v += dpp_moved<0xB1>(v);   // quad_perm 1 0 3 2
     return v;
 }
+__device__ __forceinline__ float wave_sum64(float v) { return sum_lanes<64>(v); }
 
 // The arithmetic of the row kernels, shared with the single-row product that applies the same
 // steps to its own input columns (cats_gemv_row): both must give the same bits, so the
@@ -254,7 +275,7 @@ struct ResidualNormArgs {
     const float* x_in;      // optional [T][H]: start from this instead of x
     const bf16_t* embed;    // optional [V][H]: start from embed[token[t]]
     const int32_t* token;   // device [T]
-    const float* part;      // optional [pieces][T][H] partial sums to add
+    const float* part;      // optional [pieces][T][H] partial sums to add (launch_residual_norm)
     GemmPlan plan;
     const bf16_t* gain;     // optional [H]: if given, xn = x * gain (unscaled) and ss are written
     bf16_t* xn;             // [T][H] high parts of x * gain

@@ -9,11 +9,90 @@
 
 namespace {
 
-// x[t] <- (x_in[t] | embed[token[t]] | x[t]) + sum of the GEMM pieces;  xn[t] = x[t] * gain as
-// high + low bf16 parts;  ss[t][block] = sum of x^2 over the block's columns.  One wave per
-// (row, block of 256 columns): nothing here needs a whole row, so the launch has T * H/256
-// independent waves.
-__device__ __forceinline__ void residual_norm_block(const ResidualNormArgs& a, int t, int blk) {
+// Packed X: a 128-byte line holds 16 bytes of each of eight rows.  The 16 rows of a block of
+// columns run on one XCD (workgroup b runs on XCD b % 8), so that its L2 collects the whole line: grid
+// (8 column blocks x 16 rows, groups of 8 column blocks, groups of 16 rows), column block fastest.
+dim3 packed_row_grid(int T, int H) {
+    const int n_blk = (H + SS_COLS - 1) / SS_COLS;
+    return dim3(128, (n_blk + 7) / 8, (T + 15) / 16);
+}
+
+// x[t] <- x_in[t] + sum of the GEMM pieces;  xn[t] = x[t] * gain as high + low bf16 parts;  ss[t][block] = sum of
+// x^2 over the block's columns.  One wave per (row, block of 256 columns): nothing here needs a whole row, so the
+// launch has T * H/256 independent waves.
+// What bounds it: reading the pieces (17 MB at 63 rows, 3 us) on top of an empty launch (2.2 us) and the wave's own
+// instructions at 2 ns each, the scalar loads of the arguments among them.  So the variants are templates, the number of a
+// tile's pieces comes from the host (it took two integer divisions), a piece's place is a scalar added to one 32-bit lane
+// offset, and the wave sum runs without LDS.  Launches in a layer, us: 63 rows of 4096 5.6 -> 5.2, 16 rows 5.0 as before (the
+// pieces come from memory), 15 rows of 256 3.0 -> 2.0.
+struct ResidualPartArgs {
+    const float *x_in, *part;
+    const bf16_t* gain;
+    float *x_out, *ss;
+    bf16_t *xn, *xn_lo;   // packed X: xn_lo is not used
+    int T, H;
+    int pieces[8192 / 128];   // by 128 columns
+};
+template <bool GAIN, bool XP>
+__global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualPartArgs a) {
+    const int t = XP ? blockIdx.z * 16 + blockIdx.x / 8 : blockIdx.x;
+    const int blk = XP ? blockIdx.y * 8 + blockIdx.x % 8 : blockIdx.y;
+    const int lane = threadIdx.x, j = blk * SS_COLS + 4 * lane;
+    const int T = a.T, H = a.H, na = a.pieces[2 * blk], nb = a.pieces[2 * blk + 1];
+    const float *x_in = a.x_in, *part = a.part;
+    const bf16_t* gain = a.gain;
+    // every argument is wanted here: loaded where they are used, they were six scalar round trips one behind the other
+    asm volatile("" ::"s"(T), "s"(H), "s"(na), "s"(nb), "s"(x_in), "s"(part), "s"(gain), "s"(a.x_out), "s"(a.ss), "s"(a.xn));
+    if (XP && (t >= T || blk * SS_COLS >= H)) return;
+    float ss = 0.f;
+    if (j < H) {
+        const uint32_t at = static_cast<uint32_t>(t) * H + j;   // element of an [T][H] array (T * H <= 2^20)
+        const int most = max(na, nb), mine = lane < 32 ? na : nb;
+        const size_t stride = static_cast<size_t>(T) * H;
+        f32x4 val = *reinterpret_cast<const f32x4*>(x_in + at);
+        uint2 gbits = make_uint2(0u, 0u);
+        if constexpr (GAIN) gbits = *reinterpret_cast<const uint2*>(gain + j);
+        constexpr int B = 8;
+        f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < most; s0 += 2 * B) {
+            f32x4 v[2 * B];
+#pragma unroll
+            for (int i = 0; i < B; ++i) v[i] = *reinterpret_cast<const f32x4*>(part + min(s0 + i, most - 1) * stride + at);
+            if (s0 + B < most) {
+#pragma unroll
+                for (int i = B; i < 2 * B; ++i)
+                    v[i] = *reinterpret_cast<const f32x4*>(part + min(s0 + i, most - 1) * stride + at);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < B; ++i)
+                if (s0 + i < mine) sum += v[i];
+            if (s0 + B < most) {
+#pragma unroll
+                for (int i = B; i < 2 * B; ++i)
+                    if (s0 + i < mine) sum += v[i];
+            }
+        }
+        val += sum;
+        *reinterpret_cast<f32x4*>(a.x_out + at) = val;
+        if constexpr (GAIN) {
+            ss = sum_squares4(val);
+            uint2 hi, lo;
+            gain_split4(val, gbits, hi, lo);
+            bf16_t* out = a.xn + (XP ? packed_x_offset(t, j, H) : at);
+            *reinterpret_cast<uint2*>(out) = hi;
+            *reinterpret_cast<uint2*>(XP ? out + 512 : a.xn_lo + at) = lo;
+        }
+    }
+    if constexpr (GAIN) {
+        ss = wave_sum64(ss);
+        if (lane == 0) a.ss[t * SS_STRIDE + blk] = ss;
+    }
+}
+
+// The same without pieces: x[t] <- x_in[t] | embed[token[t]] | x[t] (the caller's or the embedding rows at the start
+// of a call, or rows that only want their norm input)
+__device__ __forceinline__ void norm_block(const ResidualNormArgs& a, int t, int blk) {
     const int j = blk * SS_COLS + 4 * threadIdx.x;
     float ss = 0.f;
     if (j < a.H) {
@@ -26,11 +105,8 @@ __device__ __forceinline__ void residual_norm_block(const ResidualNormArgs& a, i
         } else {
             val = *reinterpret_cast<const f32x4*>((a.x_in ? a.x_in : a.x) + row + j);
         }
-        if (a.part) {
-            val += sum_pieces4<16>(a.part + row + j, static_cast<size_t>(a.T) * a.H, plan_pieces(a.plan, j / a.plan.bn));
-        }
         ss = sum_squares4(val);
-        if (a.embed || a.x_in || a.part) *reinterpret_cast<f32x4*>((a.x_out ? a.x_out : a.x) + row + j) = val;
+        if (a.embed || a.x_in) *reinterpret_cast<f32x4*>((a.x_out ? a.x_out : a.x) + row + j) = val;
         if (a.gain) {
             uint2 hi, lo;
             gain_split4(val, *reinterpret_cast<const uint2*>(a.gain + j), hi, lo);
@@ -44,18 +120,10 @@ __device__ __forceinline__ void residual_norm_block(const ResidualNormArgs& a, i
     ss = wave_sum64(ss);
     if (threadIdx.x == 0) a.ss[t * SS_STRIDE + blk] = ss;
 }
-// Packed X: a 128-byte line holds 16 bytes of each of eight rows.  The 16 rows of a block of
-// columns run on one XCD (workgroup b runs on XCD b % 8), so that its L2 collects the whole line.
-__device__ __forceinline__ void packed_row_block(const ResidualNormArgs& a, int b, int& t, int& blk) {
-    const int n_blk = (a.H + SS_COLS - 1) / SS_COLS;
-    const int pair = b / 128 * 8 + b % 8;   // (row group, block of columns)
-    blk = pair % n_blk;
-    t = pair / n_blk * 16 + b / 8 % 16;
-}
-__global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualNormArgs a) {
-    int t = blockIdx.x, blk = blockIdx.y;
-    if (a.xp) packed_row_block(a, blockIdx.x, t, blk);
-    if (t < a.T) residual_norm_block(a, t, blk);
+__global__ __launch_bounds__(64) void cats_norm_rows(ResidualNormArgs a) {
+    const int t = a.xp ? blockIdx.z * 16 + blockIdx.x / 8 : blockIdx.x;
+    const int blk = a.xp ? blockIdx.y * 8 + blockIdx.x % 8 : blockIdx.y;
+    if (t < a.T && blk * SS_COLS < a.H) norm_block(a, t, blk);
 }
 
 // cos/sin of pos * base^(-2j/d) for pos = ctx_len + depth[t]; computed in double so
@@ -71,16 +139,16 @@ __device__ __forceinline__ void rope_entry(const RopeTableArgs& a, int idx) {
 __global__ void cats_rope_table(RopeTableArgs a) { rope_entry(a, blockIdx.x * blockDim.x + threadIdx.x); }
 
 // The first launch of a call.  Its two halves do not depend on each other and are bound by launch latency: the rotation
-// table's workgroups (the longer ones) come first, a multiple of eight of them so that the rows' keep their XCDs.
-__global__ __launch_bounds__(64) void cats_rows_begin(ResidualNormArgs a, RopeTableArgs r, int rope_blocks) {
-    const int b = static_cast<int>(blockIdx.x) - rope_blocks;
-    if (b < 0) {
-        rope_entry(r, blockIdx.x * 64 + threadIdx.x);
+// table's workgroups (the longer ones) come first, in whole slices of the grid, so that the rows' keep their XCDs.
+__global__ __launch_bounds__(64) void cats_rows_begin(ResidualNormArgs a, RopeTableArgs r, int rope_slices) {
+    if (static_cast<int>(blockIdx.z) < rope_slices) {
+        rope_entry(r, ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 64 + threadIdx.x);
         return;
     }
-    int t = b % a.T, blk = b / a.T;
-    if (a.xp) packed_row_block(a, b, t, blk);
-    if (t < a.T) residual_norm_block(a, t, blk);
+    const int z = blockIdx.z - rope_slices;
+    const int t = a.xp ? z * 16 + blockIdx.x / 8 : blockIdx.x;
+    const int blk = a.xp ? blockIdx.y * 8 + blockIdx.x % 8 : blockIdx.y;
+    if (t < a.T && blk * SS_COLS < a.H) norm_block(a, t, blk);
 }
 
 // Adds up q|k|v partials, scales by the row's norm factor, rotates q and k (pairs j, j+d/2),
@@ -392,20 +460,38 @@ __global__ __launch_bounds__(AM_THREADS) void cats_argmax(ArgmaxArgs a) {
 
 }  // namespace
 
-static int packed_row_blocks(const ResidualNormArgs& a) {   // workgroups that packed_row_block deals out
-    const int pairs = (a.T + 15) / 16 * ((a.H + SS_COLS - 1) / SS_COLS);
-    return (pairs + 7) / 8 * 128;
-}
-
 void launch_residual_norm(const ResidualNormArgs& a, hipStream_t st) {
-    const dim3 grid = a.xp ? dim3(packed_row_blocks(a)) : dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS);
-    hipLaunchKernelGGL(cats_residual_rmsnorm, grid, dim3(64), 0, st, a);
+    const dim3 grid = a.xp ? packed_row_grid(a.T, a.H) : dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS);
+    if (!a.part) {
+        hipLaunchKernelGGL(cats_norm_rows, grid, dim3(64), 0, st, a);
+        return;
+    }
+    ResidualPartArgs p;
+    p.x_in = a.x_in ? a.x_in : a.x;
+    p.part = a.part;
+    p.gain = a.gain;
+    p.x_out = a.x_out ? a.x_out : a.x;
+    p.ss = a.ss;
+    p.xn = a.xp ? a.xp : a.xn;
+    p.xn_lo = a.xn_lo;
+    p.T = a.T;
+    p.H = a.H;
+    for (int g = 0; g < 8192 / 128; ++g)   // (places behind the last column: as that)
+        p.pieces[g] = plan_pieces(a.plan, std::min(128 * g, a.H - 1) / a.plan.bn);
+    if (!a.gain)
+        hipLaunchKernelGGL((cats_residual_rmsnorm<false, false>), dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS), dim3(64), 0, st, p);
+    else if (a.xp)
+        hipLaunchKernelGGL((cats_residual_rmsnorm<true, true>), grid, dim3(64), 0, st, p);
+    else
+        hipLaunchKernelGGL((cats_residual_rmsnorm<true, false>), grid, dim3(64), 0, st, p);
 }
 
 void launch_rows_begin(const ResidualNormArgs& a, const RopeTableArgs& r, hipStream_t st) {
-    const int rows = a.xp ? packed_row_blocks(a) : a.T * ((a.H + SS_COLS - 1) / SS_COLS);
-    const int rope = (r.T * (r.d / 2) + 511) / 512 * 8;
-    hipLaunchKernelGGL(cats_rows_begin, dim3(rope + rows), dim3(64), 0, st, a, r, rope);
+    dim3 grid = a.xp ? packed_row_grid(a.T, a.H) : dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS);
+    const int slice = 64 * grid.x * grid.y;   // table entries of one slice of the grid
+    const int rope = (r.T * (r.d / 2) + slice - 1) / slice;
+    grid.z += rope;
+    hipLaunchKernelGGL(cats_rows_begin, grid, dim3(64), 0, st, a, r, rope);
 }
 
 void launch_rope_table(const RopeTableArgs& a, hipStream_t st) {
