@@ -35,15 +35,15 @@
 
 namespace {
 
-// zero the 16-bit elements of an 8-key vector whose key index key0 + e lies outside [lo, hi)
-__device__ __forceinline__ u32x4 keep_keys(u32x4 v, int key0, int lo, int hi) {
+// which 16-bit elements of an 8-key vector belong to keys key0 + e in [lo, hi): all ones there, zero elsewhere
+__device__ __forceinline__ u32x4 keys_kept(int key0, int lo, int hi) {
+    u32x4 m;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int ka = key0 + 2 * e, kb = ka + 1;
-        if (ka < lo || ka >= hi) v[e] &= 0xFFFF0000u;
-        if (kb < lo || kb >= hi) v[e] &= 0x0000FFFFu;
+        m[e] = (ka >= lo && ka < hi ? 0x0000FFFFu : 0u) | (kb >= lo && kb < hi ? 0xFFFF0000u : 0u);
     }
-    return v;
+    return m;
 }
 
 // 16-byte device-coherent store: it goes past the XCD's L2
@@ -175,10 +175,15 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
     // stale there and come out as zeros.  Addresses are clamped into the window (what a clamp
     // moves is masked anyway: the window covers every row of the range).
     const int win_base = S & ~(ATTN_KB - 1);
-    auto mask_v = [&](bf16x8 (&v)[DB], int blk) {   // rows past the tree may hold anything
+    // (one mask of eight keys for all of a block's dims; formed at each vector, and with the ancestor bits looked up key by
+    // key, masks were more than half of the instructions, at about 2 ns each, of a block with low parts.  Launches in a
+    // layer, us: 32 heads of 128, 63 nodes / 1024 rows 14.3 -> 13.7, 128 / 512 15.9 -> 14.8, 16 / 512 8.6 as before)
+    auto keep = [](bf16x8 (&v)[DB], u32x4 m) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-            v[db] = as_bf16x8(keep_keys(__builtin_bit_cast(u32x4, v[db]), blk * ATTN_KB + 8 * q4, 0, n_keys));
+        for (int db = 0; db < DB; ++db) v[db] = as_bf16x8(__builtin_bit_cast(u32x4, v[db]) & m);
+    };
+    auto mask_v = [&](bf16x8 (&v)[DB], int blk) {   // rows past the tree may hold anything
+        if ((blk + 1) * ATTN_KB > n_keys) keep(v, keys_kept(blk * ATTN_KB + 8 * q4, 0, n_keys));
     };
     auto request_k_lo = [&](bf16x8 (&kf)[2][KS], int blk) {
         const bf16_t* kl = a.k_lo + static_cast<size_t>(h) * TREE_WIN * D;
@@ -214,11 +219,7 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
                          : vl + static_cast<size_t>(16 * db + m) * TREE_WIN + w0));
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto keep_v_lo = [&](bf16x8 (&vf)[DB], int blk) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-            vf[db] = as_bf16x8(keep_keys(__builtin_bit_cast(u32x4, vf[db]), blk * ATTN_KB + 8 * q4, a.lo_begin, a.lo_end));
-    };
+    auto keep_v_lo = [&](bf16x8 (&vf)[DB], int blk) { keep(vf, keys_kept(blk * ATTN_KB + 8 * q4, a.lo_begin, a.lo_end)); };
 
     // MODE 0: every key of the block is a context row (no mask, no tail: straight-line code);
     // MODE 1: the block may hold tree rows and rows past the tree; MODE 2: as 1, and the block
@@ -248,26 +249,20 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
         const int key0 = blk * ATTN_KB + 8 * q4;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            // this lane: query column m of group qb, keys key0 + 4*b + r
+            // this lane: query column m of group qb, keys key0 .. + 7.  Bit i of vis: key0 + i may be seen (context rows all
+            // may, tree rows by the ancestor mask, rows past the tree not: their bits are zero)
+            uint32_t vis = 0xffu;
+            if constexpr (MODE != 0) {
+                const int rel = key0 - S, w = rel >> 5;   // eight bits from bit rel of (ones below bit 0 | mask | zeros)
+                const u32x4 am = anc[qb];
+                auto word = [&](int i) { return i < 0 ? ~0u : (i == 0 ? am[0] : (i == 1 ? am[1] : (i == 2 ? am[2] : (i == 3 ? am[3] : 0u)))); };
+                vis = __builtin_amdgcn_alignbit(word(w + 1), word(w), rel & 31);
+            }
             float sc[8];
-            bool vis[8];
             float bmax = -1e30f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                bool see = true;
-                if constexpr (MODE != 0) {
-                    // branch-free: the ancestor word is picked with selects, a key outside the
-                    // tree's rows reads bit 0 of a zero word
-                    const int rel = key0 + i - S;
-                    const bool in_tree = rel >= 0 && rel < T;
-                    const int w = rel >> 5;
-                    const u32x4 am = anc[qb];
-                    uint32_t word = w == 0 ? am[0] : (w == 1 ? am[1] : (w == 2 ? am[2] : am[3]));
-                    word = in_tree ? word : 0u;
-                    see = rel < 0 || ((word >> (rel & 31)) & 1u);
-                }
-                vis[i] = see;
-                sc[i] = see ? st[qb][i >> 2][i & 3] * scale : -1e30f;
+                sc[i] = MODE == 0 || ((vis >> i) & 1u) ? st[qb][i >> 2][i & 3] * scale : -1e30f;
                 bmax = fmaxf(bmax, sc[i]);
             }
             bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
@@ -292,7 +287,7 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const float e = __builtin_amdgcn_exp2f(sc[i] - mref);
-                p[i] = (MODE == 0 || vis[i]) ? e : 0.f;
+                p[i] = MODE == 0 || ((vis >> i) & 1u) ? e : 0.f;
                 psum += p[i];
             }
             lrun[qb] += psum;
