@@ -113,8 +113,13 @@ int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_keys, in
 // 32 / 1024 (8, 4) 12.8 -> 10.5, 32 / 2000 (16, 4) 15.3 -> 14.0, 63 / 512 (9, 2) 12.6 -> 10.5, 33 / 1000 (17, 2) 13.5 -> 13.5,
 // 64 / 2048 (33, 2) 17.5 -> 21.9, 128 / 300 (14, 1) 16.1 -> 13.5, 128 / 512 (20, 1) 16.0 -> 16.0.  Attention alone: 40 heads,
 // 30 / 1500 (16, 3) 13.7 -> 14.6; 8 heads, 64 / 4096 (16, 8) 16.3 -> 14.0; 128 / 1024 (36, 1) 17.1 -> 20.1.
+// Chunks hold at least four key blocks, one for each wave (head size 64: one chunk as long as its eight waves have a block
+// each): shorter ones leave waves idle and add partial results to hand over.  In a layer, chunks down to one block -> this, us:
+// 32 heads of 128, 2 nodes / 100 rows 6.6 -> 5.4, 16 / 40 7.1 -> 4.7, 16 / 512 8.6 -> 8.0; 4 heads of 64, 15 / 128 6.4 -> 4.7,
+// 16 / 2000 9.6 -> 7.2, 30 / 300 7.2 -> 6.8; 32 of 128, 63 / 200 and 128 / 512 as before.
 void attn_split(AttnArgs& a, int n_cus, int max_chunks) {
     const int n_keys = a.ctx_len + a.T, n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
+    max_chunks = std::min(max_chunks, a.d == 64 && n_blocks <= 8 ? 1 : (n_blocks + 3) / 4);
     const int narrow = attn_chunks(a.Tq, a.nh, max_chunks, n_cus, n_keys, 16);
     a.queries = a.Tq <= 16 || n_blocks <= (narrow == 1 ? 14 : 18 * narrow - 8) ? 16 : 32;
     a.n_chunks = a.queries == 16 ? narrow : attn_chunks(a.Tq, a.nh, max_chunks, n_cus, n_keys, 32);
