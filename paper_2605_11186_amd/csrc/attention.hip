@@ -556,7 +556,7 @@ __global__ __launch_bounds__(256) void cats_decode_attention(DecodeAttnArgs a) {
     const bool builds = lane < HALF && (role == 0 || (owner && role <= 2));
     const int N = 3 * a.H;
     const int col = min(role, 2) * a.H + h * D + min(lane, HALF - 1);
-    const int pieces = plan_pieces(a.plan, col / a.plan.bn);   // both columns lie in the same tile
+    const int pieces = plan_pieces(a.plan, plan_col_tile(a.plan, col));   // both columns lie in the same tile
     float pa[PB], pb[PB];
     RowSquares sq;
     float2 cs = make_float2(1.f, 0.f);

@@ -38,6 +38,16 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast
 // whatever the shape.  A tile whose chunks are spread over several workgroups gets one
 // float32 partial result ("piece") from each of them: part[piece][t][n], piece =
 // workgroup - first workgroup of that tile.  Consumers add the pieces in index order.
+// n / d for n < 2^31 as a product and a shift: m = floor(2^(31 + l) / d) + 1 with d <= 2^l exceeds 2^(31 + l) / d by at
+// most 2^l / 2^(31 + l) of it, less than 1 / n.  A division by a number that only the launch knows is some 35 instructions on
+// the device, about 2 ns each at the head of a launch, and a workgroup of a product did four to ten of them.
+struct FastDiv {
+    uint32_t m = 1, s = 0;   // d = 1
+};
+FastDiv make_fast_div(uint32_t d);
+__host__ __device__ inline uint32_t fast_div(uint32_t n, FastDiv d) {
+    return static_cast<uint32_t>((static_cast<uint64_t>(n) * d.m) >> d.s);
+}
 struct GemmPlan {
     int bn;      // weight rows per tile
     int kc;      // k values per work item (128 or 256)
@@ -45,16 +55,18 @@ struct GemmPlan {
     int n_wgs;   // ranges of work items (one partial tile per range and tile it touches)
     int items;   // tiles * chunks
     int ts = 1;  // workgroups per range: each takes its own block of X rows (see the GEMM kernel)
+    FastDiv by_chunks, by_wgs, by_items;
 };
-// 32-bit unsigned arithmetic (a 64-bit division costs a few hundred scalar instructions on the
-// device, at the head of every launch): make_gemm_plan guarantees items * n_wgs < 2^31.
+// make_gemm_plan guarantees items * n_wgs < 2^31.
 __host__ __device__ inline int plan_owner(const GemmPlan& p, int item) {
-    return static_cast<int>((static_cast<unsigned>(item + 1) * static_cast<unsigned>(p.n_wgs) - 1u) /
-                            static_cast<unsigned>(p.items));
+    return static_cast<int>(fast_div(static_cast<unsigned>(item + 1) * static_cast<unsigned>(p.n_wgs) - 1u, p.by_items));
 }
 __host__ __device__ inline int plan_item_begin(const GemmPlan& p, int wg) {
-    return static_cast<int>(static_cast<unsigned>(wg) * static_cast<unsigned>(p.items) / static_cast<unsigned>(p.n_wgs));
+    return static_cast<int>(fast_div(static_cast<unsigned>(wg) * static_cast<unsigned>(p.items), p.by_wgs));
 }
+// tile of a column: tiles are 128 or 256 columns wide
+__host__ __device__ inline int plan_col_tile(const GemmPlan& p, int col) { return col >> (7 + (p.bn >> 8)); }
+__host__ __device__ inline int plan_tile(const GemmPlan& p, int item) { return static_cast<int>(fast_div(item, p.by_chunks)); }
 __host__ __device__ inline int plan_first_wg(const GemmPlan& p, int tile) { return plan_owner(p, tile * p.chunks); }
 __host__ __device__ inline int plan_pieces(const GemmPlan& p, int tile) {
     return plan_owner(p, tile * p.chunks + p.chunks - 1) - plan_owner(p, tile * p.chunks) + 1;
@@ -163,7 +175,7 @@ __device__ __forceinline__ f32x4 sum_pieces4(const float* p, size_t stride, int 
 
 // Sum of the pieces of column n of row t (fixed order).
 __device__ __forceinline__ float sum_pieces(const float* part, const GemmPlan& p, int T, int N, int t, int n) {
-    const int pieces = plan_pieces(p, n / p.bn);
+    const int pieces = plan_pieces(p, plan_col_tile(p, n));
     float v = 0.f;
     for (int s = 0; s < pieces; ++s) v += part[(static_cast<size_t>(s) * T + t) * N + n];
     return v;

@@ -108,7 +108,7 @@ __global__ __launch_bounds__(64 * NWR * KG) void cats_gemm_skinny_bf16(GemmArgs 
     // item (local index i) -> tile and first k of its chunk
 #define CATS_ITEM(i, tile_, k0_)                  \
     const int gi_ = item_lo + (i);                \
-    const int tile_ = static_cast<int>(static_cast<unsigned>(gi_) / static_cast<unsigned>(C)); \
+    const int tile_ = plan_tile(a.plan, gi_);     \
     const int k0_ = (gi_ - tile_ * C) * KC;
 
 #define CATS_LOAD_X(i)                                                                              \
@@ -317,7 +317,14 @@ static int plan_ts(int rows) { return rows > 96 ? 2 : 1; }
 // projection: 1376 items, 256 workgroups would run 6 items each with 10 % of the slots empty;
 // 230 workgroups run 5.98.  With pairs, target is half the workgroups and n a multiple of eight
 // (the kernel then finds a pair's range from the block index in groups of 16, one pair per XCD).
-GemmPlan make_gemm_plan(int N, int K, int target_wgs, int rows) {
+FastDiv make_fast_div(uint32_t d) {
+    if (d <= 1) return FastDiv{};
+    uint32_t l = 1;
+    while (l < 31 && (1u << l) < d) ++l;
+    return FastDiv{static_cast<uint32_t>((uint64_t{1} << (31 + l)) / d + 1), 31 + l};
+}
+
+static GemmPlan cut_ranges(int N, int K, int target_wgs, int rows) {
     GemmPlan p;
     p.bn = plan_bn(rows);
     p.kc = plan_kc(rows);
@@ -350,6 +357,14 @@ GemmPlan make_gemm_plan(int N, int K, int target_wgs, int rows) {
         }
     }
     p.n_wgs = best;
+    return p;
+}
+
+GemmPlan make_gemm_plan(int N, int K, int target_wgs, int rows) {
+    GemmPlan p = cut_ranges(N, K, target_wgs, rows);
+    p.by_chunks = make_fast_div(p.chunks);
+    p.by_wgs = make_fast_div(p.n_wgs);
+    p.by_items = make_fast_div(p.items);
     return p;
 }
 

@@ -24,6 +24,7 @@
 namespace {
 
 constexpr int GEMV_KC = 2 * GEMM_KC;   // k values per work item (the plan's kc)
+constexpr int GEMV_BN = 128;           // weight rows per tile of any single-row product (the plan's bn)
 constexpr int GEMV_XI = 32;            // work items whose input columns are held in LDS at a time
 static_assert(GEMV_KC == SS_COLS, "an item's columns are one sum-of-squares block");
 
@@ -47,8 +48,7 @@ __device__ __forceinline__ void stage_x(const GemvArgs& a, float (*xrow)[GEMV_KC
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
         it[e] = it0 + 8 * e;
-        const unsigned gi = static_cast<unsigned>(first + it[e]);
-        chunk[e] = static_cast<int>(gi % static_cast<unsigned>(C));
+        chunk[e] = first + it[e] - plan_tile(a.plan, first + it[e]) * C;
         k[e] = chunk[e] * GEMV_KC + 4 * lane;
         in_k[e] = k[e] < a.K;
         kk[e] = min(k[e], a.K - 4);   // clamped address: K is a multiple of 4
@@ -88,7 +88,7 @@ __device__ __forceinline__ void stage_x(const GemvArgs& a, float (*xrow)[GEMV_KC
 #pragma unroll
             for (int e = 0; e < NE; ++e) {
                 pp[e] = a.pend + kk[e];
-                np[e] = plan_pieces(a.pend_plan, kk[e] / a.pend_plan.bn);
+                np[e] = plan_pieces(a.pend_plan, kk[e] / GEMV_BN);
             }
             sum_pieces4_multi_hook<NE, 10>(pp, static_cast<size_t>(a.pend_ld), np, sum, hook);
         } else {
@@ -170,8 +170,8 @@ __device__ __forceinline__ void stage_x(const GemvArgs& a, float (*xrow)[GEMV_KC
         for (int e = 0; e < NE; ++e) {
             pp[2 * e] = a.pend + kk[e];
             pp[2 * e + 1] = a.pend + a.f_pad + kk[e];
-            np[2 * e] = plan_pieces(a.pend_plan, kk[e] / a.pend_plan.bn);
-            np[2 * e + 1] = plan_pieces(a.pend_plan, (a.f_pad + kk[e]) / a.pend_plan.bn);
+            np[2 * e] = plan_pieces(a.pend_plan, kk[e] / GEMV_BN);
+            np[2 * e + 1] = plan_pieces(a.pend_plan, (a.f_pad + kk[e]) / GEMV_BN);
         }
         f32x4 gu[2 * NE];
         sum_pieces4_multi_hook<2 * NE, 3>(pp, static_cast<size_t>(a.pend_ld), np, gu, hook);
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(512) void cats_gemv_row(GemvArgs a) {
 
 #define CATS_ITEM(i, tile_, k0_)                                                                        \
     const int gi_ = first + (i);                                                                        \
-    const int tile_ = static_cast<int>(static_cast<unsigned>(gi_) / static_cast<unsigned>(C));          \
+    const int tile_ = plan_tile(a.plan, gi_);                                                           \
     const int k0_ = (gi_ - tile_ * C) * GEMV_KC;
 
         // Unconditional loads at clamped addresses, as in the GEMM: columns past K meet zeros in xrow.

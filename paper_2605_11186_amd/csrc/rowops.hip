@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void cats_qkv_rope_append(QkvRopeArgs a) {
         const int vb = blockIdx.x - n_qk, slices = a.d / V_DIMS;
         const int h = vb / slices, ds = (vb - h * slices) * V_DIMS;
         const int col = 2 * a.H + h * a.d + ds + 4 * (threadIdx.x & 7);
-        const int pieces = plan_pieces(a.plan, col / a.plan.bn);
+        const int pieces = plan_pieces(a.plan, plan_col_tile(a.plan, col));
         for (int t0 = 0; t0 < a.T; t0 += 64) {   // two nodes per thread and pass
             const int ta = t0 + (threadIdx.x >> 3), tb = ta + 32;
             const int ca = min(ta, a.T - 1), cb = min(tb, a.T - 1);
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void cats_qkv_rope_append(QkvRopeArgs a) {
     {
         const float* pq = a.part + static_cast<size_t>(t) * N + c0;
         const float* const pp[4] = {pq, pq + half, pq + a.H, pq + a.H + half};
-        const int nq = plan_pieces(a.plan, c0 / a.plan.bn), nk = plan_pieces(a.plan, (a.H + c0) / a.plan.bn);
+        const int nq = plan_pieces(a.plan, plan_col_tile(a.plan, c0)), nk = plan_pieces(a.plan, plan_col_tile(a.plan, a.H + c0));
         const int np[4] = {nq, nq, nk, nk};
         sum_pieces4_multi<4, 8>(pp, stride, np, v4);
     }
@@ -270,7 +270,7 @@ __global__ void cats_swiglu(SwigluArgs a) {
     // n % 4 == 0 and the tile height is a multiple of 4: the four columns share a tile
     const RowSquares sq = row_squares_load(a.ns, t);
     const float* const pp[2] = {p, p + a.f_pad};
-    const int np[2] = {plan_pieces(a.plan, n / a.plan.bn), plan_pieces(a.plan, (a.f_pad + n) / a.plan.bn)};
+    const int np[2] = {plan_pieces(a.plan, plan_col_tile(a.plan, n)), plan_pieces(a.plan, plan_col_tile(a.plan, a.f_pad + n))};
     f32x4 gu[2];
     sum_pieces4_multi<2, 4>(pp, stride, np, gu);
     uint2 hi, lo;
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(AM_THREADS) void cats_argmax(ArgmaxArgs a) {
         const size_t stride = static_cast<size_t>(a.T) * a.ld;
         for (int g = g_begin + tid; g < g_end; g += AM_THREADS) {
             const int v = 4 * g;   // the four columns share a tile (tile heights are multiples of 4)
-            f32x4 val = sum_pieces4(a.part + static_cast<size_t>(t) * a.ld + v, stride, plan_pieces(a.plan, v / a.plan.bn));
+            f32x4 val = sum_pieces4(a.part + static_cast<size_t>(t) * a.ld + v, stride, plan_pieces(a.plan, plan_col_tile(a.plan, v)));
             val *= rs;
             if (a.logits) {
                 if (a.V % 4 == 0) {
@@ -477,7 +477,7 @@ void launch_residual_norm(const ResidualNormArgs& a, hipStream_t st) {
     p.T = a.T;
     p.H = a.H;
     for (int g = 0; g < 8192 / 128; ++g)   // (places behind the last column: as that)
-        p.pieces[g] = plan_pieces(a.plan, std::min(128 * g, a.H - 1) / a.plan.bn);
+        p.pieces[g] = plan_pieces(a.plan, plan_col_tile(a.plan, std::min(128 * g, a.H - 1)));
     if (!a.gain)
         hipLaunchKernelGGL((cats_residual_rmsnorm<false, false>), dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS), dim3(64), 0, st, p);
     else if (a.xp)
