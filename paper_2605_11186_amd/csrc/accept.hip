@@ -125,6 +125,9 @@ __global__ __launch_bounds__(CATS_MAX_TREE) void cats_typical_edges(TypicalArgs 
 // Row ctx_len + path[k] -> row ctx_len + k for k = 0..n-1, one workgroup per (layer, head, keys or
 // values): keys are [row][dim], values [dim][row]; thread dd owns one head dimension, reads all its source
 // elements first and only then writes, so overlapping source/destination rows cannot clobber each other.
+// Rows that stay where they are (the root's always) are not read: bound by the 128-byte line that every (layer, head,
+// dimension) of the values costs, 26 MB for 40 layers of 40 heads.  cats_accept_compact, reading every row of the path ->
+// this, us: that shape with nothing accepted 11.0 -> 5.1, 32 layers of 32 heads with four nodes accepted 12.3 -> 10.9.
 __device__ __forceinline__ void compact_rows(const CompactArgs& a, int n, const int32_t* committed) {
     const int l = blockIdx.x, h = blockIdx.y, which = blockIdx.z, dd = threadIdx.x;
     int path[CATS_MAX_DEPTH + 1];
@@ -135,18 +138,18 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int n, const 
         bf16_t* base = a.k[l] + (static_cast<size_t>(h) * a.max_ctx + a.ctx_len) * a.d + dd;
 #pragma unroll
         for (int k = 0; k <= CATS_MAX_DEPTH; ++k)
-            if (k < n) val[k] = base[static_cast<size_t>(path[k]) * a.d];
+            if (path[k] != k) val[k] = base[static_cast<size_t>(path[k]) * a.d];
 #pragma unroll
         for (int k = 0; k <= CATS_MAX_DEPTH; ++k)
-            if (k < n && path[k] != k) base[static_cast<size_t>(k) * a.d] = val[k];
+            if (path[k] != k) base[static_cast<size_t>(k) * a.d] = val[k];
     } else {
         bf16_t* base = a.v[l] + (static_cast<size_t>(h) * a.d + dd) * a.max_ctx + a.ctx_len;
 #pragma unroll
         for (int k = 0; k <= CATS_MAX_DEPTH; ++k)
-            if (k < n) val[k] = base[path[k]];
+            if (path[k] != k) val[k] = base[path[k]];
 #pragma unroll
         for (int k = 0; k <= CATS_MAX_DEPTH; ++k)
-            if (k < n && path[k] != k) base[k] = val[k];
+            if (path[k] != k) base[k] = val[k];
     }
 }
 
