@@ -512,8 +512,8 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
 //   scores: a key row is D/8 16-byte pieces, one per lane, summed over those lanes;
 //   values: the cache is transposed, a dim's 128 keys are 16 16-byte pieces, one per lane.
 // Rows that must stay invisible (later siblings, rows past the tree, the node's own row, which is
-// being written meanwhile) are excluded by selects, never by a multiplication with zero; a tile of context rows alone
-// has none and goes without.
+// being written meanwhile) are excluded by selects, never by a multiplication with zero, and so are rows whose weight has
+// underflowed to zero, whatever their values hold; a tile of context rows with no zero weight goes without.
 // What bounds it: an empty launch takes 2.2 us, the memory round trip 3 and a wave's instructions 2 ns each, 7 of 10 us
 // with no key, value or partial sum loaded.  So: as few instructions as possible (no selects in full tiles, sums over 16
 // lanes on the vector ALU instead of shuffles through LDS) and not more workgroups than compute units where avoidable (the
@@ -677,7 +677,11 @@ __global__ __launch_bounds__(256) void cats_decode_attention(DecodeAttnArgs a) {
         const float m_new = fmaxf(m_run, m_t);
         const float c_run = __builtin_amdgcn_exp2f(m_run - m_new), c_t = __builtin_amdgcn_exp2f(m_t - m_new);
         float acc[VP];
-        if (full) {
+        // (every wave holds all of the tile's weights; a zero one, hidden or underflowed, must not meet an infinite value)
+        float least = pw[0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) least = fminf(least, pw[e]);
+        if (full && __builtin_amdgcn_ballot_w64(least == 0.f) == 0) {
 #pragma unroll
             for (int p = 0; p < VP; ++p) {
                 acc[p] = 0.f;

@@ -37,3 +37,27 @@ def test_root_and_later_nodes(pair, S):
         got = out.cpu().numpy()
         # rows of earlier nodes come back from the bf16 cache, so later queries see them at 2^-9
         assert rel_err(got, want[n - 1: n]) <= (TOL if n == 1 else 2.0 ** -8), (n, S)
+
+
+@pytest.mark.parametrize("S", [100, 128, 200, 1300])
+def test_values_behind_a_zero_weight_do_not_count(pair, S):
+    """Two opposite keys so long that one of them takes the whole weight of the first tile (partly filled at 100 rows, full
+    beyond), in every head: the other rows of that tile, whose weights underflow to zero, may hold anything."""
+    kc, vc = pair.oracle_cache_random(4, S)
+    ks, vs = pair.device_cache_from_oracle(kc, vc, S)
+    a, b, tile = 5, 77, min(S, 128)
+    ks[0][:, a] *= 2.0 ** 20   # (so long that it takes no luck of the head's query)
+    ks[0][:, b] = -ks[0][:, a]
+    others = [r for r in range(tile) if r not in (a, b)]
+
+    def rows():
+        cats.cats_set_tree(pair.ctx, np.array([5], np.int32), np.array([-1], np.int32), np.array([0], np.int32))
+        out = torch.full((1, pair.dims.hidden), float("nan"), device="cuda")
+        cats.cats_verify_nodes(pair.ctx, pair.layers_arr, 0, 1, pair.d_embed, None, cats.kv_array(ks, vs), S, 0, out)
+        return out.cpu()
+
+    want = rows()
+    assert torch.isfinite(want).all()
+    for anything in (float("inf"), float("-inf"), float("nan")):
+        vs[0][:, :, others] = anything
+        assert torch.equal(rows(), want), anything
