@@ -98,31 +98,10 @@ inline size_t align256(size_t n) { return (n + 255) & ~static_cast<size_t>(255);
 // register footprint lets one 512-thread workgroup live on a CU); cats_create reads the count.
 int target_wgs(const cats_ctx* c) { return c->n_cus; }
 
-// Key chunks per (head, query group): the launch has heads * query groups * chunks workgroups,
-// about one per compute unit; more chunks than that only add hand-over traffic between workgroups.
-int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_keys, int queries) {
-    const int n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
-    const int groups = (rows + queries - 1) / queries;
-    const int chunks = std::max(1, n_cus / std::max(1, n_heads * groups));
-    return std::min(chunks, std::min(n_blocks, max_chunks));
-}
-// Queries of a workgroup.  With 16 a wave has half the arithmetic and half the partial results to hand over, and registers
-// to request all of a block with low parts at once; beyond 16 rows every 16 of them then read all keys and values, which is
-// the shorter way while a chunk has few key blocks (fewer where one chunk needs no hand-over with 16 but has all the keys).
-// In a layer, 32 then 16 queries, us (32 heads of 128; in brackets blocks a chunk, chunks): 20 nodes / 300 rows 11.7 -> 7.9,
-// 32 / 1024 (8, 4) 12.8 -> 10.5, 32 / 2000 (16, 4) 15.3 -> 14.0, 63 / 512 (9, 2) 12.6 -> 10.5, 33 / 1000 (17, 2) 13.5 -> 13.5,
-// 64 / 2048 (33, 2) 17.5 -> 21.9, 128 / 300 (14, 1) 16.1 -> 13.5, 128 / 512 (20, 1) 16.0 -> 16.0.  Attention alone: 40 heads,
-// 30 / 1500 (16, 3) 13.7 -> 14.6; 8 heads, 64 / 4096 (16, 8) 16.3 -> 14.0; 128 / 1024 (36, 1) 17.1 -> 20.1.
-// Chunks hold at least four key blocks, one for each wave (head size 64: one chunk as long as its eight waves have a block
-// each): shorter ones leave waves idle and add partial results to hand over.  In a layer, chunks down to one block -> this, us:
-// 32 heads of 128, 2 nodes / 100 rows 6.6 -> 5.4, 16 / 40 7.1 -> 4.7, 16 / 512 8.6 -> 8.0; 4 heads of 64, 15 / 128 6.4 -> 4.7,
-// 16 / 2000 9.6 -> 7.2, 30 / 300 7.2 -> 6.8; 32 of 128, 63 / 200 and 128 / 512 as before.
-void attn_split(AttnArgs& a, int n_cus, int max_chunks) {
-    const int n_keys = a.ctx_len + a.T, n_blocks = (n_keys + ATTN_KB - 1) / ATTN_KB;
-    max_chunks = std::min(max_chunks, a.d == 64 && n_blocks <= 8 ? 1 : (n_blocks + 3) / 4);
-    const int narrow = attn_chunks(a.Tq, a.nh, max_chunks, n_cus, n_keys, 16);
-    a.queries = a.Tq <= 16 || n_blocks <= (narrow == 1 ? 14 : 18 * narrow - 8) ? 16 : 32;
-    a.n_chunks = a.queries == 16 ? narrow : attn_chunks(a.Tq, a.nh, max_chunks, n_cus, n_keys, 32);
+void set_split(AttnArgs& a, int n_cus, int max_chunks) {
+    const AttnSplit sp = attn_split(a.nh, a.d, a.Tq, a.ctx_len + a.T, n_cus, max_chunks);
+    a.queries = sp.queries;
+    a.n_chunks = sp.chunks;
     a.t_pad = (a.Tq + 31) / 32 * 32;
 }
 
@@ -311,7 +290,7 @@ void enqueue_attention(cats_ctx* c, const bf16_t* q, const bf16_t* q_lo, const c
     a.d = c->d.head_dim;
     a.max_ctx = c->d.max_ctx;
     a.ctx_len = ctx_len;
-    attn_split(a, c->n_cus, c->attn_max_chunks);
+    set_split(a, c->n_cus, c->attn_max_chunks);
     a.po = c->attn_po;
     a.pml = c->attn_pml;
     a.out = out;
@@ -1355,7 +1334,7 @@ int cats_tree_attention_noalloc(const void* q, const cats_kv_layer* kv, const in
     a.d = head_dim;
     a.max_ctx = max_ctx;
     a.ctx_len = ctx_len;
-    attn_split(a, dev->n_cus, 32);
+    set_split(a, dev->n_cus, 32);
     // layout of the scratch array: tree arrays, ancestor masks, then the chunk partials
     size_t off = 0;
     auto take = [&](size_t bytes) {

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_split.hpp"
 #include "cats.h"
 
 typedef uint16_t bf16_t;  // raw bf16 bits
@@ -463,7 +464,6 @@ void launch_gemv(const GemvArgs& a, hipStream_t st, hipEvent_t ev_start = nullpt
 // r - (ctx_len & ~31), i.e. the window starts at the 32-key block that holds row ctx_len, which
 // keeps 8-key vector loads 16-byte aligned.  Entries outside [lo_begin, lo_end) are stale.
 constexpr int TREE_WIN = 32 + CATS_MAX_TREE;   // rows of the window
-constexpr int ATTN_KB = 32;      // keys per block
 constexpr int ATTN_MAX_QGROUPS = CATS_MAX_TREE / 16;   // query groups per head at most
 struct AttnArgs {
     const bf16_t* q;        // [Tq][H]
