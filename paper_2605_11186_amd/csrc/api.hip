@@ -298,8 +298,7 @@ void enqueue_attention(cats_ctx* c, const bf16_t* q, const bf16_t* q_lo, const c
 }
 
 // The attention block of a single-row call: q|k|v from the product's partial sums, cache append
-// and attention over the context and the node's own path in one kernel.  Key chunks of at least
-// four 32-key blocks, as many as the context's scratch holds at most.  Returns the number of
+// and attention over the context and the node's own path in one kernel.  Returns the number of key
 // chunks: the product that follows merges their results (gemv_attn).
 int enqueue_row_attention(cats_ctx* c, const float* part, const GemmPlan& plan, const cats_kv_layer* kv,
                            int ctx_len, hipStream_t st) {
@@ -317,13 +316,9 @@ int enqueue_row_attention(cats_ctx* c, const float* part, const GemmPlan& plan, 
     a.d = c->d.head_dim;
     a.max_ctx = c->d.max_ctx;
     a.ctx_len = ctx_len;
-    // (the node's own row comes beside the last chunk's keys)
-    const int n_blocks = std::max(1, (ctx_len + c->n0 + ATTN_KB - 1) / ATTN_KB);
-    const int per_chunk = std::max(DEC_TILE / ATTN_KB, (n_blocks + DEC_MAX_CHUNKS - 1) / DEC_MAX_CHUNKS);
-    a.n_chunks = (n_blocks + per_chunk - 1) / per_chunk;
-    // a last chunk of one block goes to the one before it where it would only make workgroups share compute units
-    if (a.n_chunks > 1 && n_blocks % per_chunk == 1 && a.n_chunks * a.nh > c->n_cus) --a.n_chunks;
-    a.span = per_chunk * ATTN_KB;
+    const RowSplit sp = row_split(ctx_len + c->n0);   // (the node's own row comes beside the last chunk's keys)
+    a.n_chunks = sp.chunks;
+    a.span = sp.span;
     a.po = c->attn_po;
     a.pml = c->attn_pml;
     launch_decode_attention(a, st);

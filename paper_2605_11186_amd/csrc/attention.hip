@@ -518,8 +518,8 @@ __global__ __launch_bounds__(64 * W) void cats_tree_attention_kernel(AttnArgs a)
 // with no key, value or partial sum loaded.  So: as few instructions as possible (no selects in full tiles, sums over 16
 // lanes on the vector ALU instead of shuffles through LDS) and not more workgroups than compute units where avoidable (the
 // node's own row is nobody's chunk: behind 1024 rows 32 heads have 256 workgroups, not 288).  32 heads of 128, launches in
-// a layer, us: 1024 rows 10.1 -> 6.7, 1024 + 1 to 5 nodes 9.7 -> 8.0; the output projection behind it, merging eight chunks
-// instead of nine, 9.9 -> 9.3.
+// a layer, us: 1024 rows 9.9 -> 6.7, 1024 + 1 to 5 nodes 9.6 -> 7.5; the output projection behind it 9.8 -> 9.0 where it merges
+// eight chunks instead of nine, 9.9 -> 9.4 with nine.
 __device__ __forceinline__ bool mask_bit(const u32x4& m, int i) {
     const uint32_t w = i < 64 ? (i < 32 ? m[0] : m[1]) : (i < 96 ? m[2] : m[3]);
     return (w >> (i & 31)) & 1u;

@@ -39,3 +39,22 @@ inline AttnSplit attn_split(int n_heads, int head_dim, int rows, int n_keys, int
     if (rows <= 16 || (fits && n_blocks <= (narrow == 1 ? 14 : 18 * narrow - 8))) return {16, narrow};
     return {32, attn_chunks(rows, n_heads, max_chunks, n_cus, n_keys, 32)};
 }
+
+constexpr int DEC_TILE = 128;       // keys per pass of a workgroup
+constexpr int DEC_MAX_CHUNKS = 32;  // key chunks per head at most (the context's scratch holds that many)
+
+struct RowSplit {
+    int chunks;   // per head
+    int span;     // keys per chunk; the last one holds what is left
+};
+
+// Chunks of a single query: one pass each up to 4096 keys, beyond that as few blocks more as 32 chunks need.  A short last
+// chunk stays a workgroup of its own also where the chip is full: handed to the chunk before it, it is that workgroup's second
+// pass (its loads, scores and sums once more, one after the other), which takes longer than the workgroups saved.  In layers of
+// one row (attention and its products), merged -> this, us: 32 heads of 128, 1025 to 1056 rows 38.5 -> 37.7, 1281 to 1312
+// 39.3 -> 38.0; 40 heads, 2049 rows 55.0 -> 52.6; 64 heads of 64, 650 rows 36.3 -> 35.2.
+inline RowSplit row_split(int n_keys) {
+    const int n_blocks = std::max(1, (n_keys + ATTN_KB - 1) / ATTN_KB);
+    const int per_chunk = std::max(DEC_TILE / ATTN_KB, (n_blocks + DEC_MAX_CHUNKS - 1) / DEC_MAX_CHUNKS);
+    return {(n_blocks + per_chunk - 1) / per_chunk, per_chunk * ATTN_KB};
+}

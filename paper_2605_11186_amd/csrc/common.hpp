@@ -491,8 +491,6 @@ struct AttnArgs {
 // cache (bf16) and uses them (high + low part) without reading them back.  The kernel ends with
 // one partial result per (head, key chunk); the output projection that follows merges them while
 // it builds its input columns (GEMV_ATTN), so no workgroup waits for another.
-constexpr int DEC_TILE = 128;       // keys per pass of a workgroup
-constexpr int DEC_MAX_CHUNKS = 32;  // key chunks per head at most (the context's scratch holds that many)
 struct DecodeAttnArgs {
     const float* part;   // [pieces][3H] partial sums of q | k | v, still to be scaled by the row's norm factor
     GemmPlan plan;

@@ -17,6 +17,11 @@ extern "C" void tree_split(int heads, int d, int rows, int keys, int cus, int ma
     out[0] = s.queries;
     out[1] = s.chunks;
 }
+extern "C" void row_split_of(int keys, int* out) {
+    const RowSplit s = row_split(keys);
+    out[0] = s.chunks;
+    out[1] = s.span;
+}
 """)
 
 
@@ -53,3 +58,14 @@ def test_32_queries_where_16_were_slower(shim, heads, d, rows, ctx):
                                               (64, 64, 64, 128), (40, 128, 96, 128), (128, 64, 32, 128)])
 def test_16_queries_where_32_were_slower(shim, heads, d, rows, ctx):
     assert tree(shim, heads, d, rows, ctx)[0] == 16
+
+
+def test_a_single_query_has_chunks_of_one_pass(shim):
+    out = (C.c_int * 2)()
+    for keys in [*range(0, 10000), 40000, 2 ** 25]:
+        shim.row_split_of(keys, out)
+        chunks, span = out
+        assert 1 <= chunks <= MAX_CHUNKS and span % 32 == 0
+        assert (chunks - 1) * span < max(keys, 1) <= chunks * span   # every chunk has keys, none more than the span
+        if keys <= 128 * MAX_CHUNKS:
+            assert span == 128
