@@ -1047,11 +1047,13 @@ int cats_draft_chain(cats_ctx* ctx, const cats_layer_weights* layers, int32_t la
         // the row after the draft layers is written straight into hidden_out: by the adapter's first
         // product, which carries out the last layer's residual update, or by a row kernel at the end
         float* h_k = hidden_out ? hidden_out + k * H : nullptr;
-        if (k == gamma) {
-            finish_row(ctx, h_k, nullptr, st);
-            break;
-        }
-        enqueue_layer_row(ctx, adapter, kv_adapter, ctx_len, h_k, st);
+        float* direct = aligned16(hidden_out) ? h_k : nullptr;
+        if (k == gamma)
+            finish_row(ctx, direct ? direct : ctx->row.x, nullptr, st);
+        else
+            enqueue_layer_row(ctx, adapter, kv_adapter, ctx_len, direct, st);
+        if (h_k && !direct) HIP_TRY(hipMemcpyAsync(h_k, ctx->row.x, sizeof(float) * H, hipMemcpyDeviceToDevice, st));
+        if (k == gamma) break;
         ctx->row.next_gain = g_adapter_out;
         enqueue_lm_head(ctx, w_lm, nullptr, ctx->token + k + 1, nullptr, st);
     }

@@ -1,13 +1,13 @@
 """Where a call leaves its final rows: the last launch writes them straight into hidden_out when that is 16-byte
-aligned and any layer ran, a copy does otherwise.  Both ways, in place on hidden_in too, must give the same bits; the
-cache rows after the joint walk-and-roll-back launch must be those of the walk followed by the roll-back."""
+aligned and any layer ran, a copy does otherwise.  Both ways, in place on hidden_in too, must give the same bits, in the
+draft chain as well; the cache rows after the joint walk-and-roll-back launch must be those of the walk followed by the roll-back."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2605_11186_amd as cats
 import synth
-from gpu_common import Pair
+from gpu_common import Pair, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 SEED, S = 31, 70
@@ -48,6 +48,29 @@ def test_hidden_out_anywhere_gives_the_same_rows(pair, T, layers, verify):
     # from the caller's rows, in place: the rows that the embedding table would have given
     rows(pair, T, 0, aligned, None, verify)
     assert np.array_equal(rows(pair, T, layers, aligned, aligned, verify), want)
+
+
+@pytest.mark.parametrize("layers", [1, 2])
+def test_draft_chain_leaves_its_rows_anywhere(pair, layers):
+    d, gamma = pair.dims, 5
+    ad = synth.adapter_weights(d, SEED, 0)
+    adapter = cats.pack_layer({k: to_dev_bf16(v) for k, v in ad.items() if k != "g_out"})
+    adapter_arr, g_out = cats.layer_array([adapter]), to_dev_bf16(ad["g_out"])
+    got = []
+    for shift in (0, 1, 2):
+        ks, vs = pair.device_cache_from_oracle(*pair.oracle_cache_random(SEED, S), S)
+        ka, va = ks[0].clone(), vs[0].clone()
+        buf = torch.full(((gamma + 1) * d.hidden + 4,), float("nan"), device="cuda")
+        rows = buf[shift: (gamma + 1) * d.hidden + shift].view(gamma + 1, d.hidden)
+        tokens = torch.zeros(gamma + 1, dtype=torch.int32, device="cuda")
+        cats.cats_draft_chain(pair.ctx, pair.layers_arr, 0, layers, adapter_arr, g_out, pair.d_final["w_lm"], pair.d_embed,
+                              cats.kv_array(ks, vs), cats.kv_array([ka], [va]), S, 3, gamma, tokens, hidden_out=rows)
+        torch.cuda.synchronize()
+        assert torch.isnan(buf[:shift]).all() and torch.isnan(buf[rows.numel() + shift:]).all()
+        got.append((rows.clone(), tokens.clone(), ks[0].view(torch.int16).clone(), vs[0].view(torch.int16).clone()))
+    assert torch.isfinite(got[0][0]).all()
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
 
 
 @pytest.mark.parametrize("T,layers", [(1, 2), (2, 2), (33, 1), (64, 2)])
