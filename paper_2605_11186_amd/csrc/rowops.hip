@@ -31,14 +31,14 @@ struct ResidualPartArgs {
     float *x_out, *ss;
     bf16_t *xn, *xn_lo;   // packed X: xn_lo is not used
     int T, H;
-    int pieces[8192 / 128];   // by 128 columns
+    int pieces[8192 / 128];   // by 128 columns, as far as there are columns
 };
 template <bool GAIN, bool XP>
 __global__ __launch_bounds__(64) void cats_residual_rmsnorm(ResidualPartArgs a) {
     const int t = XP ? blockIdx.z * 16 + blockIdx.x / 8 : blockIdx.x;
     const int blk = XP ? blockIdx.y * 8 + blockIdx.x % 8 : blockIdx.y;
     const int lane = threadIdx.x, j = blk * SS_COLS + 4 * lane;
-    const int T = a.T, H = a.H, na = a.pieces[2 * blk], nb = a.pieces[2 * blk + 1];
+    const int T = a.T, H = a.H, na = a.pieces[2 * blk], nb = a.pieces[2 * blk + 1];   // (any numbers where there are no columns)
     const float *x_in = a.x_in, *part = a.part;
     const bf16_t* gain = a.gain;
     // every argument is wanted here: loaded where they are used, they were six scalar round trips one behind the other
@@ -476,7 +476,7 @@ void launch_residual_norm(const ResidualNormArgs& a, hipStream_t st) {
     p.xn_lo = a.xn_lo;
     p.T = a.T;
     p.H = a.H;
-    for (int g = 0; g < 8192 / 128; ++g)   // (places behind the last column: as that)
+    for (int g = 0; g < (a.H + SS_COLS - 1) / SS_COLS * 2; ++g)   // (a place behind the last column: as that)
         p.pieces[g] = plan_pieces(a.plan, plan_col_tile(a.plan, std::min(128 * g, a.H - 1)));
     if (!a.gain)
         hipLaunchKernelGGL((cats_residual_rmsnorm<false, false>), dim3(a.T, (a.H + SS_COLS - 1) / SS_COLS), dim3(64), 0, st, p);
