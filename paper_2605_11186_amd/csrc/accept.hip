@@ -153,7 +153,10 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int n, const 
     }
 }
 
-__global__ void cats_kv_compact(CompactArgs a) { compact_rows(a, a.res->n_accepted + 1, a.res->path); }
+// The roll-back alone, along the path of an earlier walk.
+__global__ void cats_kv_compact(CompactArgs a, const cats_accept_result* res) {
+    compact_rows(a, res->n_accepted + 1, res->path);
+}
 
 // The walk and the roll-back behind it in one launch: every workgroup walks the tree for itself (a few hundred bytes
 // of L2 hits and at most 2 * CATS_MAX_DEPTH dependent LDS reads), the first one writes the result.  Bound by latency;
@@ -185,6 +188,6 @@ void launch_typical_edges(const TypicalArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(cats_typical_edges, dim3(1), dim3(CATS_MAX_TREE), 0, st, a);
 }
 
-void launch_compact(const CompactArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(cats_kv_compact, dim3(a.n_layers, a.nh, 2), dim3(a.d), 0, st, a);
+void launch_compact(const CompactArgs& a, const cats_accept_result* res, hipStream_t st) {
+    hipLaunchKernelGGL(cats_kv_compact, dim3(a.n_layers, a.nh, 2), dim3(a.d), 0, st, a, res);
 }

@@ -556,8 +556,7 @@ void enqueue_lm_head(cats_ctx* c, const void* w_lm, float* logits_out, int32_t* 
     }
 }
 
-CompactArgs compact_args(const cats_ctx* c, const cats_kv_layer* kv, int layer_begin, int layer_end, int ctx_len,
-                         const cats_accept_result* res_dev) {
+CompactArgs compact_args(const cats_ctx* c, const cats_kv_layer* kv, int layer_begin, int layer_end, int ctx_len) {
     CompactArgs ca;
     ca.n_layers = layer_end - layer_begin;
     for (int l = layer_begin; l < layer_end; ++l) {
@@ -568,7 +567,6 @@ CompactArgs compact_args(const cats_ctx* c, const cats_kv_layer* kv, int layer_b
     ca.d = c->d.head_dim;
     ca.max_ctx = c->d.max_ctx;
     ca.ctx_len = ctx_len;
-    ca.res = res_dev;
     return ca;
 }
 
@@ -586,7 +584,7 @@ int enqueue_accept_compact(cats_ctx* c, const int32_t* amax, const cats_kv_layer
     aa.out = out_dev;
     // a lone root is committed where it is: nothing to roll back
     if (layer_end > layer_begin && c->T > 1)
-        launch_accept_compact(aa, compact_args(c, kv, layer_begin, layer_end, ctx_len, out_dev), st);
+        launch_accept_compact(aa, compact_args(c, kv, layer_begin, layer_end, ctx_len), st);
     else
         launch_accept(aa, st);
     HIP_TRY(hipGetLastError());
@@ -979,7 +977,7 @@ int cats_compact_along(cats_ctx* ctx, const cats_accept_result* result_dev, cons
         return CATS_EINVAL;
     if (layer_end > layer_begin && !kv_ok(kv, layer_begin, layer_end)) return CATS_EINVAL;
     if (layer_end > layer_begin)
-        launch_compact(compact_args(ctx, kv, layer_begin, layer_end, ctx_len, result_dev), as_stream(stream));
+        launch_compact(compact_args(ctx, kv, layer_begin, layer_end, ctx_len), result_dev, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return CATS_OK;
 }

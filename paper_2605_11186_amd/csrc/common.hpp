@@ -164,13 +164,12 @@ __device__ __forceinline__ void sum_pieces4_multi_hook(const float* const (&p)[G
     }
 }
 
-// Sum of `pieces` 16-byte groups p[s * stride] (fixed order), B loads in flight.
-template <int B = 8>
+// Sum of `pieces` 16-byte groups p[s * stride] (fixed order), eight loads in flight.
 __device__ __forceinline__ f32x4 sum_pieces4(const float* p, size_t stride, int pieces) {
     const float* const pp[1] = {p};
     const int np[1] = {pieces};
     f32x4 acc[1];
-    sum_pieces4_multi<1, B>(pp, stride, np, acc);
+    sum_pieces4_multi<1, 8>(pp, stride, np, acc);
     return acc[0];
 }
 
@@ -284,7 +283,7 @@ __device__ __forceinline__ f32x4 join_bf4(uint2 hi, uint2 lo) {
 
 struct ResidualNormArgs {
     float* x;               // [T][H] residual stream, in/out
-    float* x_out = nullptr; // if given, the updated rows go here instead of back to x (16-byte aligned)
+    float* x_out = nullptr; // with part, if given: the updated rows go here instead of back to x (16-byte aligned)
     const float* x_in;      // optional [T][H]: start from this instead of x
     const bf16_t* embed;    // optional [V][H]: start from embed[token[t]]
     const int32_t* token;   // device [T]
@@ -546,7 +545,6 @@ struct CompactArgs {
     bf16_t* v[CATS_MAX_LAYERS];
     int n_layers;  // entries used
     int nh, d, max_ctx, ctx_len;
-    const cats_accept_result* res;   // cats_kv_compact: the path to roll back along
 };
-void launch_compact(const CompactArgs& a, hipStream_t st);
+void launch_compact(const CompactArgs& a, const cats_accept_result* res, hipStream_t st);
 void launch_accept_compact(const AcceptArgs& w, const CompactArgs& a, hipStream_t st);

@@ -106,7 +106,7 @@ __device__ __forceinline__ void norm_block(const ResidualNormArgs& a, int t, int
             val = *reinterpret_cast<const f32x4*>((a.x_in ? a.x_in : a.x) + row + j);
         }
         ss = sum_squares4(val);
-        if (a.embed || a.x_in) *reinterpret_cast<f32x4*>((a.x_out ? a.x_out : a.x) + row + j) = val;
+        if (a.embed || a.x_in) *reinterpret_cast<f32x4*>(a.x + row + j) = val;
         if (a.gain) {
             uint2 hi, lo;
             gain_split4(val, *reinterpret_cast<const uint2*>(a.gain + j), hi, lo);
