@@ -102,6 +102,7 @@ void set_split(AttnArgs& a, int n_cus, int max_chunks) {
     const AttnSplit sp = attn_split(a.nh, a.d, a.Tq, a.ctx_len + a.T, n_cus, max_chunks);
     a.queries = sp.queries;
     a.n_chunks = sp.chunks;
+    a.waves = sp.waves;
     a.t_pad = (a.Tq + 31) / 32 * 32;
 }
 

@@ -14,7 +14,7 @@
 // What bounds it: at short contexts a chain of memory round trips (queries and first block, values with
 // low parts, hand-over between chunks), at long ones the waves' arithmetic and the 128-byte lines a compute
 // unit can have in flight.  One register set: the next block's keys and values are requested into the registers that
-// this block's products have just freed.  Four or eight waves, see launch_attention.  With eight waves and head_dim 128
+// this block's products have just freed.  Four or eight waves, see attn_waves.  With eight waves and head_dim 128
 // the 256 registers of a wave do not quite do: 10 spill around the run of blocks with low parts (at most one or two blocks of a
 // wave), none in the context loop.  Four waves of 64 queries (half the key and value traffic) were slower than
 // eight waves of 32 at every size: 33.3 against 25.8 us at 64 nodes / 4096 rows, 26.2 against 18.3 at 63 / 1024.
@@ -753,26 +753,20 @@ void launch_decode_attention(const DecodeAttnArgs& a, hipStream_t st) {
         hipLaunchKernelGGL((cats_decode_attention<64>), grid, dim3(256), 0, st, a);
 }
 
-// Waves per workgroup.  Head size 128: four, without a spill; eight where a head has more than eight chunks, which its
-// last workgroup then merges in more than one round (twice the threads halve that).  Launches inside a layer, four with
-// two register sets (as it was) -> eight -> four, us: 32 heads, 16 nodes / 512 rows 14.5 -> 13.6 -> 12.5, 33 / 97 13.4 -> 13.8 -> 11.7, 63 /
-// 1024 18.4 -> 17.3 -> 15.2, 63 / 4096 29.6 -> 29.8 -> 25.9, 128 / 4096 47.6 -> 46.6 -> 44.1; 8 heads, 16 nodes (32 chunks at 1024 rows and
-// more) / 512 rows 15.7 -> 13.9 -> 14.4, / 4096 21.5 -> 17.6 -> 19.0.  Head size 64 (no spill, half the LDS): eight, by 2.5 to 4 %.
 void launch_attention(const AttnArgs& a, hipStream_t st) {
-    const int qn = a.queries;
-    const dim3 grid(a.n_chunks, a.nh, (a.Tq + qn - 1) / qn);
+    const dim3 grid(a.n_chunks, a.nh, (a.Tq + a.queries - 1) / a.queries);
 #define CATS_ATTN(DV, QBV, WV) hipLaunchKernelGGL((cats_tree_attention_kernel<DV, QBV, WV>), grid, dim3(64 * WV), 0, st, a)
-    if (qn == 16) {
+    if (a.queries == 16) {
         if (a.d == 64)
             CATS_ATTN(64, 1, 8);
-        else if (a.n_chunks > 8)
+        else if (a.waves == 8)
             CATS_ATTN(128, 1, 8);
         else
             CATS_ATTN(128, 1, 4);
     } else {
         if (a.d == 64)
             CATS_ATTN(64, 2, 8);
-        else if (a.n_chunks > 8)
+        else if (a.waves == 8)
             CATS_ATTN(128, 2, 8);
         else
             CATS_ATTN(128, 2, 4);

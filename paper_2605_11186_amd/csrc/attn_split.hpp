@@ -7,6 +7,7 @@ constexpr int ATTN_KB = 32;   // keys per block
 struct AttnSplit {
     int queries;   // of a workgroup: 16 or 32
     int chunks;    // key chunks per (head, query group)
+    int waves;     // of a workgroup: 4 or 8
 };
 
 // Key chunks per (head, query group): the launch has heads * query groups * chunks workgroups,
@@ -17,6 +18,12 @@ inline int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_k
     const int chunks = std::max(1, n_cus / std::max(1, n_heads * groups));
     return std::min(chunks, std::min(n_blocks, max_chunks));
 }
+// Waves per workgroup.  Head size 128: four, without a spill; eight where a head has more than eight chunks, which its
+// last workgroup then merges in more than one round (twice the threads halve that).  Launches inside a layer, four with
+// two register sets (as it was) -> eight -> four, us: 32 heads, 16 nodes / 512 rows 14.5 -> 13.6 -> 12.5, 33 / 97 13.4 -> 13.8 -> 11.7, 63 /
+// 1024 18.4 -> 17.3 -> 15.2, 63 / 4096 29.6 -> 29.8 -> 25.9, 128 / 4096 47.6 -> 46.6 -> 44.1; 8 heads, 16 nodes (32 chunks at 1024 rows and
+// more) / 512 rows 15.7 -> 13.9 -> 14.4, / 4096 21.5 -> 17.6 -> 19.0.  Head size 64 (no spill, half the LDS): eight, by 2.5 to 4 %.
+inline int attn_waves(int head_dim, int chunks) { return head_dim == 64 || chunks > 8 ? 8 : 4; }
 // Queries of a workgroup.  With 16 a wave has half the arithmetic and half the partial results to hand over, and registers
 // to request all of a block with low parts at once; beyond 16 rows every 16 of them then read all keys and values, which is
 // the shorter way while a chunk has few key blocks (fewer where one chunk needs no hand-over with 16 but has all the keys).
@@ -36,8 +43,9 @@ inline AttnSplit attn_split(int n_heads, int head_dim, int rows, int n_keys, int
     max_chunks = std::min(max_chunks, head_dim == 64 && n_blocks <= 8 ? 1 : (n_blocks + 3) / 4);
     const int narrow = attn_chunks(rows, n_heads, max_chunks, n_cus, n_keys, 16);
     const bool fits = static_cast<long>(n_heads) * ((rows + 15) / 16) <= n_cus;
-    if (rows <= 16 || (fits && n_blocks <= (narrow == 1 ? 14 : 18 * narrow - 8))) return {16, narrow};
-    return {32, attn_chunks(rows, n_heads, max_chunks, n_cus, n_keys, 32)};
+    const int queries = rows <= 16 || (fits && n_blocks <= (narrow == 1 ? 14 : 18 * narrow - 8)) ? 16 : 32;
+    const int chunks = queries == 16 ? narrow : attn_chunks(rows, n_heads, max_chunks, n_cus, n_keys, 32);
+    return {queries, chunks, attn_waves(head_dim, chunks)};
 }
 
 constexpr int DEC_TILE = 128;       // keys per pass of a workgroup

@@ -475,7 +475,7 @@ struct AttnArgs {
     const u32x4* anc;       // device [T] ancestor-or-self masks (cats_tree_upload)
     int T, H, nh, d, max_ctx, ctx_len;   // T: tree nodes whose K/V rows ctx_len.. take part as keys
     int Tq, q0;             // the queries are nodes q0 .. q0+Tq-1 (rows 0..Tq-1 of q / out)
-    int queries;            // of a workgroup: 16 or 32
+    int queries, waves;     // of a workgroup: 16 or 32, 4 or 8
     int n_chunks, t_pad;    // key chunks per (head, query group); rows per (head, chunk) in po / pml
     float* po;              // [nh][n_chunks][t_pad][d]
     float* pml;             // [nh][n_chunks][t_pad][2]

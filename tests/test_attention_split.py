@@ -4,6 +4,7 @@ import ctypes as C
 import pytest
 
 import host_shim
+from test_gpu_attention_variants import CASES
 
 CUS, MAX_CHUNKS = 256, 32
 
@@ -16,6 +17,7 @@ extern "C" void tree_split(int heads, int d, int rows, int keys, int cus, int ma
     const AttnSplit s = attn_split(heads, d, rows, keys, cus, max_chunks);
     out[0] = s.queries;
     out[1] = s.chunks;
+    out[2] = s.waves;
 }
 extern "C" void row_split_of(int keys, int* out) {
     const RowSplit s = row_split(keys);
@@ -26,7 +28,8 @@ extern "C" void row_split_of(int keys, int* out) {
 
 
 def tree(shim, heads, d, rows, ctx, cus=CUS):
-    out = (C.c_int * 2)()
+    """queries, chunks, waves"""
+    out = (C.c_int * 3)()
     shim.tree_split(heads, d, rows, ctx + rows, cus, MAX_CHUNKS, out)
     return tuple(out)
 
@@ -37,15 +40,22 @@ def test_16_query_workgroups_beyond_16_rows_fit_the_compute_units(shim):
             for heads in [*range(1, 129), 200, 1000]:
                 for rows in range(1, 129):
                     for ctx in (0, 40, 300, 700, 2100, 4096):
-                        queries, chunks = tree(shim, heads, d, rows, ctx, cus)
+                        queries, chunks, waves = tree(shim, heads, d, rows, ctx, cus)
                         groups, blocks = -(-rows // queries), -(-(ctx + rows) // 32)
-                        assert queries in (16, 32) and 1 <= chunks <= min(MAX_CHUNKS, blocks)
+                        assert (d, queries, waves) in CASES and 1 <= chunks <= min(MAX_CHUNKS, blocks)
                         if rows <= 16:
                             assert queries == 16
                         elif queries == 16:
                             assert heads * groups * chunks <= cus
                         if chunks > 1:
                             assert heads * groups * chunks <= cus
+
+
+def test_every_variant_has_a_size_of_several_chunks(shim):
+    for (d, queries, waves), sizes in CASES.items():
+        for heads, rows, ctx in sizes:
+            q, chunks, w = tree(shim, heads, d, rows, ctx)
+            assert (q, w) == (queries, waves) and chunks > 1, (heads, d, rows, ctx, q, chunks, w)
 
 
 @pytest.mark.parametrize("heads,d,rows,ctx", [(64, 64, 65, 300), (64, 64, 128, 40), (40, 128, 97, 8), (40, 128, 128, 300), (64, 128, 96, 128),

@@ -91,7 +91,10 @@ def test_value_rows_past_32_bit_element_offsets():
 
 
 @pytest.mark.parametrize("heads,d,T,S", [(28, 128, 32, 1500), (32, 128, 32, 1500), (8, 128, 64, 700), (8, 128, 65, 700),
-                                         (28, 128, 3, 255), (28, 128, 2, 286), (1, 128, 128, 4000)])
+                                         (28, 128, 3, 255), (28, 128, 2, 286), (1, 128, 128, 4000),
+                                         (8, 128, 16, 1000), (8, 128, 16, 1100), (8, 128, 16, 1500),
+                                         (8, 128, 64, 3500), (8, 128, 80, 3140), (8, 128, 80, 3500), (8, 128, 97, 3500)])
 def test_both_wave_counts(heads, d, T, S):
-    """Either side of the line between four and eight waves: by heads, by query groups and by key blocks."""
+    """Either side of the line between four and eight waves (more than eight chunks a head): by heads, by query groups and by
+    key blocks.  Eight waves of 16 queries: one head, and 8 heads with 16 nodes; of 32 queries: 8 heads with 80 nodes."""
     test_long_chunks(heads, d, T, S)
