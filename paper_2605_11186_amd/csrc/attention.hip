@@ -14,9 +14,9 @@
 // What bounds it: at short contexts a chain of memory round trips (queries and first block, values with
 // low parts, hand-over between chunks), at long ones the waves' arithmetic and the 128-byte lines a compute
 // unit can have in flight.  One register set: the next block's keys and values are requested into the registers that
-// this block's products have just freed.  Four or eight waves, see attn_waves.  With eight waves and head_dim 128
-// the 256 registers of a wave do not quite do: 10 spill around the run of blocks with low parts (at most one or two blocks of a
-// wave), none in the context loop.  Four waves of 64 queries (half the key and value traffic) were slower than
+// this block's products have just freed.  Four or eight waves, see attn_waves.  With eight waves, head_dim 128
+// and 32 queries the 256 registers of a wave do not quite do: 16 spill around the run of blocks with low parts (at most one or two
+// blocks of a wave), none in the context loop.  Four waves of 64 queries (half the key and value traffic) were slower than
 // eight waves of 32 at every size: 33.3 against 25.8 us at 64 nodes / 4096 rows, 26.2 against 18.3 at 63 / 1024.
 // Scores are computed transposed, S^T = K Q^T, with the 16x16x32 bf16 MFMA, so a
 // lane owns ONE query column and 8 keys of every 32-key block: the running

@@ -18,11 +18,14 @@ inline int attn_chunks(int rows, int n_heads, int max_chunks, int n_cus, int n_k
     const int chunks = std::max(1, n_cus / std::max(1, n_heads * groups));
     return std::min(chunks, std::min(n_blocks, max_chunks));
 }
-// Waves per workgroup.  Head size 128: four, without a spill; eight where a head has more than eight chunks, which its
-// last workgroup then merges in more than one round (twice the threads halve that).  Launches inside a layer, four with
-// two register sets (as it was) -> eight -> four, us: 32 heads, 16 nodes / 512 rows 14.5 -> 13.6 -> 12.5, 33 / 97 13.4 -> 13.8 -> 11.7, 63 /
-// 1024 18.4 -> 17.3 -> 15.2, 63 / 4096 29.6 -> 29.8 -> 25.9, 128 / 4096 47.6 -> 46.6 -> 44.1; 8 heads, 16 nodes (32 chunks at 1024 rows and
-// more) / 512 rows 15.7 -> 13.9 -> 14.4, / 4096 21.5 -> 17.6 -> 19.0.  Head size 64 (no spill, half the LDS): eight, by 2.5 to 4 %.
+// Waves per workgroup.  Head size 64: eight (no spill, half the LDS), 2.5 to 4 % faster than four.  Head size 128: four,
+// which need no spill; eight where a head has more than eight chunks, which its last workgroup then merges in more than one
+// round (twice the threads halve that).  Eight -> four, us.  Up to eight chunks, alone: 32 queries, 8 heads, 97 nodes / 3500
+// rows 16.7 -> 15.9; 16 queries, 32 heads, 16 / 512 7.8 -> 7.5, 64 / 1000 14.4 -> 13.8.  Beyond eight, 16 queries, whole
+// attention blocks (low parts of the own rows included): 8 heads, 16 / 2000 (16 chunks) 22.9 -> 23.6, 16 / 4096 (16) 26.5 -> 27.8;
+// alone the two are within 5 % either way (8 heads, 16 / 1500 9.0 -> 8.8, 16 / 4096 13.2 -> 13.8).  32 queries have more than
+// eight chunks with few heads, many nodes and long contexts only; there four would be ahead with 8 heads (80 / 3500, ten chunks,
+// alone 15.6 -> 14.9) and behind with 4 (80 / 3500, 21 chunks, 15.3 -> 15.9).
 inline int attn_waves(int head_dim, int chunks) { return head_dim == 64 || chunks > 8 ? 8 : 4; }
 // Queries of a workgroup.  With 16 a wave has half the arithmetic and half the partial results to hand over, and registers
 // to request all of a block with low parts at once; beyond 16 rows every 16 of them then read all keys and values, which is
@@ -34,8 +37,10 @@ inline int attn_waves(int head_dim, int chunks) { return head_dim == 64 || chunk
 // Not where 16-query workgroups outnumber the compute units: some of those then take two in turn, and 32 queries fit.
 // Alone, 32 then 16 queries, us: 40 heads of 128, 112 nodes / 8 rows 6.6 -> 8.8, 128 / 128 8.6 -> 11.8, 128 / 300 11.7 -> 17.2;
 // 64 heads of 64, 80 / 128 6.0 -> 7.6, 96 / 300 7.4 -> 10.9; 128 heads of 64, 65 / 40 (neither fits) 8.4 -> 8.3.
-// Chunks hold at least four key blocks, one for each wave (head size 64: one chunk as long as its eight waves have a block
-// each): shorter ones leave waves idle and add partial results to hand over.  In a layer, chunks down to one block -> this, us:
+// Chunks hold about four key blocks or more: the number of chunks is the blocks over four, rounded up, and the kernel deals
+// them out by cost (a block with tree rows counts twice), so that 17 blocks are chunks of 4, 4, 3, 4 and 2.  Shorter ones leave
+// more waves without a block and add partial results to hand over.  (Eight waves have a block each from eight blocks a chunk
+// on; head size 64 stays with one chunk that far.)  In a layer, chunks down to one block -> this, us:
 // 32 heads of 128, 2 nodes / 100 rows 6.6 -> 5.4, 16 / 40 7.1 -> 4.7, 16 / 512 8.6 -> 8.0; 4 heads of 64, 15 / 128 6.4 -> 4.7,
 // 16 / 2000 9.6 -> 7.2, 30 / 300 7.2 -> 6.8; 32 of 128, 63 / 200 and 128 / 512 as before.
 inline AttnSplit attn_split(int n_heads, int head_dim, int rows, int n_keys, int n_cus, int max_chunks) {

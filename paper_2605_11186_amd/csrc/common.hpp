@@ -5,6 +5,7 @@
 
 #include "attn_split.hpp"
 #include "cats.h"
+#include "fast_div.hpp"
 
 typedef uint16_t bf16_t;  // raw bf16 bits
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -39,16 +40,6 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast
 // whatever the shape.  A tile whose chunks are spread over several workgroups gets one
 // float32 partial result ("piece") from each of them: part[piece][t][n], piece =
 // workgroup - first workgroup of that tile.  Consumers add the pieces in index order.
-// n / d for n < 2^31 as a product and a shift: m = floor(2^(31 + l) / d) + 1 with d <= 2^l exceeds 2^(31 + l) / d by at
-// most 2^l / 2^(31 + l) of it, less than 1 / n.  A division by a number that only the launch knows is some 35 instructions on
-// the device, about 2 ns each at the head of a launch, and a workgroup of a product did four to ten of them.
-struct FastDiv {
-    uint32_t m = 1, s = 0;   // d = 1
-};
-FastDiv make_fast_div(uint32_t d);
-__host__ __device__ inline uint32_t fast_div(uint32_t n, FastDiv d) {
-    return static_cast<uint32_t>((static_cast<uint64_t>(n) * d.m) >> d.s);
-}
 struct GemmPlan {
     int bn;      // weight rows per tile
     int kc;      // k values per work item (128 or 256)

@@ -317,13 +317,6 @@ static int plan_ts(int rows) { return rows > 96 ? 2 : 1; }
 // projection: 1376 items, 256 workgroups would run 6 items each with 10 % of the slots empty;
 // 230 workgroups run 5.98.  With pairs, target is half the workgroups and n a multiple of eight
 // (the kernel then finds a pair's range from the block index in groups of 16, one pair per XCD).
-FastDiv make_fast_div(uint32_t d) {
-    if (d <= 1) return FastDiv{};
-    uint32_t l = 1;
-    while (l < 31 && (1u << l) < d) ++l;
-    return FastDiv{static_cast<uint32_t>((uint64_t{1} << (31 + l)) / d + 1), 31 + l};
-}
-
 static GemmPlan cut_ranges(int N, int K, int target_wgs, int rows) {
     GemmPlan p;
     p.bn = plan_bn(rows);
