@@ -488,7 +488,7 @@ RopeTableArgs rope_table_args(const cats_ctx* c, int ctx_len) {
     return r;
 }
 
-// Rows that a kernel can write with 16-byte stores; any other place gets them by a copy.
+// hidden_out that a kernel can write with 16-byte stores; any other place gets its rows by a copy.
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // typical: also the per-node log-sum-exp / entropy and, per node, whether its token passes the
